@@ -113,7 +113,8 @@ typedef struct mist_space_desc {
                             the struct) turns the weight-sampled argmins off */
   const double* alphas;  /* host: the samples alpha_a in [0, 1] (any order, repeats allowed) */
   int64_t tile_configs;  /* launch geometry, results do not depend on it: configurations per
-                            full-size tile of the evaluation kernel, at least (0: 16384) */
+                            full-size tile of the evaluation kernel, at least (0: 32768,
+                            more in spaces of over 131,072 configurations per resident wave) */
   int32_t max_blocks;    /* cap on the evaluation kernel's grid (0: every block that fits on the
                             device at once) */
   int32_t cand_window;   /* exact frontier, results do not depend on it: each tile first writes
@@ -200,8 +201,11 @@ mist_status mist_space_create(const mist_model_desc* m, const mist_hw_desc* hw, 
                               const mist_space_desc* s, const mist_allocator* alloc,
                               mist_space** out);
 
-/* Enqueues the evaluation of every configuration (cost model, feasibility filter, per
- * bucket and per group reductions; Sec. 5.3, Eq. 4-6, Algorithm 1) on hip_stream
+/* Enqueues the search of the whole space (cost model, feasibility filter, per bucket and per
+ * group reductions; Sec. 5.3, Eq. 4-6, Algorithm 1): the results are those of evaluating every
+ * configuration.  Large spaces are searched with bounds: configurations whose memory is over the
+ * budget, or whose objective is provably above the least already found for their bucket, are
+ * decided without forming their times.  Runs on hip_stream
  * (a hipStream_t; NULL = the null stream) and returns without waiting.  Re-runnable; each
  * run overwrites the previous results.  On a stream other than the one of the space's
  * previous evaluation or exact frontier, it first waits on the host for the work queued

@@ -43,6 +43,12 @@ constexpr int64_t kExact = (int64_t)1 << 53;  // integers below this convert to 
 constexpr int64_t kStaticStrips = 512;        // strips per resident wave up to which a space is
                                               // cut into one tile per wave
 constexpr int64_t kMinTileConfigs = 16384;    // configurations per tile of a larger space, at least
+constexpr int64_t kMinBoundedConfigs = 32768; // the same in the bounded search
+constexpr int64_t kTilesPerWave = 4;          // full-size tiles per resident wave there, at most about
+// Spaces that the bounded search evaluates: enough configurations that the bounds exclude more than
+// they cost, and large enough groups (use_bounds).
+constexpr uint64_t kBoundedConfigs = 120000000, kBoundedPerGroup = 8000;
+constexpr uint64_t kBoundedAlphaConfigs = 250000000, kBoundedAlphaPerGroup = 30000;
 constexpr int64_t kMaxTiles = 131072;         // and tiles per space, at most
 constexpr int64_t kWindowDiv = 8;             // exact frontier: candidate window of a tile,
                                               // 1/kWindowDiv of its configurations
@@ -50,6 +56,31 @@ constexpr int64_t kWindowSlots = (int64_t)1 << 27;  // and all windows together,
 constexpr int64_t kPoolSlots = (int64_t)1 << 27;    // overflow pool of the candidate pass, at most
 constexpr int64_t kTailPercent = 10;          // share of each group's strips in small tiles
 constexpr int64_t kStripAlign = kWaveTile;    // strips per tile: a multiple of the wave
+
+// Least directional derivative of Algorithm 1's time along (0, 0, 1, 1), both host streams growing
+// alike.  For a given order in which the streams finish, the time is linear in the stream times:
+// each phase lasts the scaled time of the stream that finishes, and every other member's standalone
+// time falls by that length over its factor.  The time is continuous where orders change (a phase of
+// length 0), so along a segment it never grows by less than the least slope over the orders it meets:
+// all (first = 0), those that start with GPU-GPU (1), or with GPU-GPU and then compute (2).
+double host_slope(const double phi[16][4], int first) {
+  int ord[4] = {0, 1, 2, 3};
+  double least = std::numeric_limits<double>::infinity();
+  do {
+    if ((first >= 1 && ord[0] != 1) || (first >= 2 && ord[1] != 0)) continue;
+    double x[4] = {0.0, 0.0, 1.0, 1.0}, T = 0.0;
+    int mask = 15;
+    for (int i = 0; i < 3; ++i) {
+      const double ov = x[ord[i]] * phi[mask][ord[i]];
+      T += ov;
+      for (int j = 0; j < 4; ++j)
+        if (mask >> j & 1) x[j] -= ov / phi[mask][j];
+      mask &= ~(1 << ord[i]);
+    }
+    least = std::min(least, T + x[ord[3]]);
+  } while (std::next_permutation(ord, ord + 4));
+  return least - 1e-9 * (1.0 + std::fabs(least));
+}
 
 int popcount4(int v) { return (v & 1) + ((v >> 1) & 1) + ((v >> 2) & 1) + ((v >> 3) & 1); }
 
@@ -73,6 +104,7 @@ struct mist_space {
   DevModel dm;
   uint64_t n_configs = 0;
   int32_t strips_per_tile = 0;
+  bool bounded = false;  // evaluated by the bounded search (use_bounds)
   // memory
   mist_allocator alloc{};
   bool custom_alloc = false;
@@ -87,10 +119,12 @@ struct mist_space {
   int32_t* d_pk_group = nullptr;
   int32_t* d_work = nullptr;
   int32_t eval_grid = 0;
-  int64_t tile_configs = 0;  // configurations per full-size tile, at least
+  int64_t tile_configs = 0;  // configurations per full-size tile, at least (0: chosen by the space's size)
   int32_t max_blocks = 0;    // cap on the evaluation grid (0: none)
   int32_t cand_window = 0;   // exact frontier: window divisor (0: automatic)
   int32_t max_group_tiles = 0;  // tiles (full-size and small) of the largest group
+  unsigned long long* d_thr = nullptr;  // per group and bucket: the smallest objective known so far
+  unsigned long long* d_athr = nullptr; // per group and weight sample: order key of the smallest value
   double* d_part_obj = nullptr;
   uint64_t* d_part_id = nullptr;
   double* d_bucket_obj = nullptr;
@@ -441,6 +475,11 @@ std::string enumerate(mist_space* S, mist_status* code) {
     // every rounding error involved and is far below a bucket width), so one comparison
     // with E_j settles the bucket.
     d.kNB = ((double)S->NB / h.mem_bytes) * (1.0 - 0x1p-40);
+    d.lbs = 1.0 - 0x1p-30;
+    for (int mask = 0; mask < 16; ++mask)
+      for (int j = 0; j < 4; ++j)
+        if (popcount4(mask) >= 2 && (mask >> j & 1) && h.phi[mask][j] > 0x1p16) d.lbs = 0.0;
+    for (int f = 0; f < 3; ++f) d.slope[f] = host_slope(h.phi, f);
     for (int j = 0; j < MIST_MAX_MB; ++j) d.ieta[j] = 0.0;
     for (size_t j = 0; j < S->mb.size(); ++j) {
       if (h.eta_max == 0.0) {  // measured efficiency of this microbatch size
@@ -497,11 +536,14 @@ mist::EvalArgs eval_args(const mist_space* S) {
   a.ratio = S->d_ratio;
   a.R = S->R;
   a.NB = S->NB;
+  a.bounded = S->bounded ? 1 : 0;
   a.n_tiles = (int32_t)S->tiles.size();
   a.n_groups = (int64_t)S->groups.size();
   a.n_configs = S->n_configs;
   a.part_obj = S->d_part_obj;
   a.part_id = S->d_part_id;
+  a.thr = S->d_thr;
+  a.athr = S->d_athr;
   a.pk = S->d_pk;
   a.pk_group = S->d_pk_group;
   a.n_pk = (int32_t)S->pk_group.size();
@@ -612,6 +654,18 @@ mist_status fill_results(mist_space* S, const uint64_t* ids, const double* objs,
 
 namespace {
 
+// Whether the bounded search evaluates the space, or every configuration is evaluated.  Measured over
+// spaces of 1e6 to 3e9 configurations (evaluation kernel, every configuration / bounded search): with
+// buckets alone 0.5-1.1x below 1e8, 1.2-1.9x from 1.2e8 to 3e8, 2-12x above 6e8; below about 8,000
+// configurations per group the tables and the seeds of a group cost more than its bounds save
+// (0.55x at 1,500, 0.97x at 8,400).  With weight samples, whose smallest delta is hard to bound, 0.5-1.0x
+// below 2.5e8 or about 30,000 configurations per group (0.88x at 21,000), 1.2-2.2x above.
+bool use_bounds(const mist_space* S) {
+  const uint64_t n = S->n_configs, g = (uint64_t)S->groups.size();
+  if (S->A > 0) return g > 0 && n >= kBoundedAlphaConfigs && n / g >= kBoundedAlphaPerGroup;
+  return g > 0 && n >= kBoundedConfigs && n / g >= kBoundedPerGroup;
+}
+
 // Tiles: contiguous strips of one group, at most strips_per_tile each (a multiple of the wave
 // width).  Every wave of the persistent evaluation grid takes tile number (its global wave
 // index) first and claims further tiles from the device counter, in tile order.  A space of
@@ -634,12 +688,15 @@ std::string build_tiles(mist_space* S, int64_t resident_waves) {
     if (v > (uint64_t)INT32_MAX / 2) v = (uint64_t)INT32_MAX / 2 / kStripAlign * kStripAlign;
     return v;
   };
-  const bool single = total_strips <= W * (uint64_t)kStaticStrips;
+  const bool single = !S->bounded && total_strips <= W * (uint64_t)kStaticStrips;
   uint64_t spt;
   if (single)
     spt = align((total_strips + W - 1) / W);
   else
-    spt = align(std::max<uint64_t>(((uint64_t)S->tile_configs + R2 - 1) / R2,
+    spt = align(std::max<uint64_t>(S->tile_configs > 0 ? ((uint64_t)S->tile_configs + R2 - 1) / R2
+                               : S->bounded ? std::max<uint64_t>(((uint64_t)kMinBoundedConfigs + R2 - 1) / R2,
+                                                                 total_strips / (W * kTilesPerWave))
+                                            : ((uint64_t)kMinTileConfigs + R2 - 1) / R2,
                                    (total_strips + (uint64_t)kMaxTiles - 1) / (uint64_t)kMaxTiles));
   const uint64_t spt_tail = single ? spt : align(spt / 4);
   S->strips_per_tile = (int32_t)spt;
@@ -742,7 +799,7 @@ mist_status mist_space_create(const mist_model_desc* m, const mist_hw_desc* hw, 
     S->l_rule = s->l_rule;
     S->ratio_om.assign(s->ratios, s->ratios + s->n_ratios);
     for (int32_t i = 0; i < s->n_ratios; ++i) S->ratio_om.push_back(1.0 - s->ratios[i]);
-    S->tile_configs = s->tile_configs > 0 ? s->tile_configs : kMinTileConfigs;
+    S->tile_configs = s->tile_configs;
     S->max_blocks = s->max_blocks;
     S->cand_window = s->cand_window;
     S->A = s->n_alphas;
@@ -758,6 +815,7 @@ mist_status mist_space_create(const mist_model_desc* m, const mist_hw_desc* hw, 
       delete S;
       return fail(ecode, err);
     }
+    S->bounded = use_bounds(S);
     mist_status rc = MIST_OK;
     // Persistent evaluation grid: as many blocks as fit on the device at once.
     int64_t resident_blocks = 1;
@@ -766,7 +824,7 @@ mist_status mist_space_create(const mist_model_desc* m, const mist_hw_desc* hw, 
       hipError_t e = hipGetDevice(&dev);
       if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
       if (e != hipSuccess) rc = fail_hip(e, "device attributes");
-      const int per_cu = eval_blocks_per_cu(S->R, S->A > 0 ? kModeAlpha : kModeBuckets);
+      const int per_cu = eval_blocks_per_cu(S->R, S->A > 0 ? kModeAlpha : kModeBuckets, S->bounded);
       resident_blocks = std::max<int64_t>(1, (int64_t)cus * (per_cu > 0 ? per_cu : 1));
       if (S->max_blocks > 0) resident_blocks = std::min<int64_t>(resident_blocks, S->max_blocks);
       S->cus = cus;
@@ -802,6 +860,11 @@ mist_status mist_space_create(const mist_model_desc* m, const mist_hw_desc* hw, 
       if (!S->d_pk || !S->d_work) rc = fail(MIST_E_NOMEM, "device allocation failed: pair constants");
     }
     const size_t nt = S->tiles.size(), ng = S->groups.size();
+    if (!rc && S->bounded) {
+      S->d_thr = (unsigned long long*)dev_alloc(S, ng * 64 * sizeof(uint64_t), nullptr);
+      if (S->A > 0) S->d_athr = (unsigned long long*)dev_alloc(S, ng * (size_t)S->A * sizeof(uint64_t), nullptr);
+      if (!S->d_thr || (S->A > 0 && !S->d_athr)) rc = fail(MIST_E_NOMEM, "device allocation failed: thresholds");
+    }
     if (!rc) {
       S->d_part_obj = (double*)dev_alloc(S, nt * 64 * sizeof(double), nullptr);
       S->d_part_id = (uint64_t*)dev_alloc(S, nt * 64 * sizeof(uint64_t), nullptr);
@@ -872,6 +935,10 @@ mist_status mist_eval_space(mist_space* S, void* hip_stream) {
     const hipError_t e = hipEventRecord(ev[0], st);
     if (e != hipSuccess) return fail_hip(e, "hipEventRecord");
   }
+  if (ea.thr) {
+    rc = launch_eval(ea, (int)((ea.n_groups + kWaves - 1) / kWaves), S->A > 0 ? kModeSeedAlpha : kModeSeed, st);
+    if (rc) return fail_hip((hipError_t)rc, "seed kernel launch");
+  }
   rc = launch_eval(ea, S->eval_grid, S->A > 0 ? kModeAlpha : kModeBuckets, st);
   if (rc) return fail_hip((hipError_t)rc, "evaluation kernel launch");
   if (ev) {
@@ -909,7 +976,7 @@ mist_status mist_eval_space(mist_space* S, void* hip_stream) {
 
 // Grid of the persistent evaluation kernel in a given variant.
 static int32_t mode_grid(const mist_space* S, int mode) {
-  const int per_cu = eval_blocks_per_cu(S->R, mode);
+  const int per_cu = eval_blocks_per_cu(S->R, mode, S->bounded);
   int64_t resident = std::max<int64_t>(1, (int64_t)S->cus * (per_cu > 0 ? per_cu : 1));
   if (S->max_blocks > 0) resident = std::min<int64_t>(resident, S->max_blocks);
   const int64_t waves_needed = (int64_t)(S->tiles.size() + kWaves - 1) / kWaves;

@@ -52,6 +52,11 @@ struct DevHw {
   double iF, iP, iL;         // 1 / FLOP/s, 1 / PCIe, 1 / link
   double M;                  // memory budget
   double kNB;                // NB / M * (1 - 2^-40): floor(mem * kNB) is the bucket or one below
+  double lbs;                // objective bounds are lowered by this factor: 1 - 2^-30, or 0 (no bound)
+                             // with slowdown factors above 2^16
+  double slope[3];           // least growth of Algorithm 1's time when both host streams grow by one:
+                             // over all orders in which the streams finish, those in which GPU-GPU
+                             // is first, and those in which compute follows it
   double ieta[MIST_MAX_MB];  // 1 / eta(b) per microbatch index
   double edge[MIST_MAX_BUCKETS];     // E_j; +inf past NB
   // Row per co-running pattern (bit j = stream j runs): phi[4] then psi[4].  Patterns of
@@ -91,6 +96,9 @@ constexpr int kModeBuckets = 0;  // bucket minima (and per-tile partials)
 constexpr int kModeAlpha = 1;    // bucket minima and the weight-sampled argmins
 constexpr int kModeEmit = 2;     // exact frontier: write and count each tile's candidates
 constexpr int kModeDump = 3;     // per-configuration values of listed tiles (parity checks)
+constexpr int kModeSeed = 4;     // first thresholds of every group from a sample of its strips
+constexpr int kModeSeedAlpha = 5;  // the same with weight samples
+constexpr int kSeedIters = 1;    // 64 strips each
 constexpr int kDumpWords = 6;    // doubles per configuration in the dump variant's output
 
 struct EvalArgs {
@@ -103,6 +111,7 @@ struct EvalArgs {
   const DevHw* hws;
   const double* ratio;   // r[0..R), then om[0..R) = 1 - r
   int32_t R, NB;
+  int32_t bounded;       // the bounded search (large spaces), or every configuration evaluated
   int32_t n_tiles;
   int32_t* work;         // tile counters of the persistent evaluation kernel, kClaimCounters
                          // of them kCounterStride apart (reset by K0)
@@ -110,6 +119,8 @@ struct EvalArgs {
   uint64_t n_configs;
   double* part_obj;      // [n_tiles][64]
   uint64_t* part_id;     // [n_tiles][64]
+  unsigned long long* thr;  // [n_groups][64] bits of the smallest objective known per bucket, or nullptr
+  unsigned long long* athr; // [n_groups][n_alpha] order keys of the smallest weighted values known, or nullptr
   PairK* pk;             // [n_pk] pair constants, group-major
   const int32_t* pk_group;  // [n_pk] group of each entry
   int32_t n_pk;
@@ -183,7 +194,7 @@ int noalloc_scratch(void** ptr);
 // Kernel launchers (mist_kernels.hip).
 int launch_pairs(const EvalArgs& a, void* stream);
 int launch_eval(const EvalArgs& a, int blocks, int mode, void* stream);
-int eval_blocks_per_cu(int R, int mode);
+int eval_blocks_per_cu(int R, int mode, bool bounded);
 int launch_reduce(const ReduceArgs& a, void* stream);
 int launch_eval_ids(const EvalArgs& a, const uint64_t* ids, int64_t n, double* out, void* stream);
 // Tiles that may hold a candidate of the exact frontier, from the last evaluation's partials.

@@ -372,21 +372,15 @@ __device__ __forceinline__ double interference_known(const KnownRow& r, double h
 // Algorithm 1 for the first n of the N configurations of an activation-ratio block (host streams
 // h[c], d[c]), one wave-uniform choice of form per configuration (measured fastest against one
 // choice per block or half block: 0.81 against 1.16 and 1.02 ms on gpt2.7b-d16, equal on the
-// Llama spaces).  With SKIP a configuration free in every lane is not evaluated, and every free
-// lane's result is NaN.
-template <int N, bool SKIP = false>
+// Llama spaces).
+template <int N>
 __device__ __forceinline__ void interference_known_n(const KnownRow& r, const double (&h)[N], const double (&d)[N],
                                                      const bool (&free)[N], double (&out)[N], int (&form)[N], int n,
                                                      const double* __restrict__ tab, const RowK& K) {
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     if (c >= n) break;
-    form[c] = 0;
-    if (SKIP && !__builtin_amdgcn_ballot_w64(!free[c]))  // every lane's result is unused: none is formed
-      out[c] = __builtin_nan("");
-    else
-      out[c] = interference_known(r, h[c], d[c], free[c], tab, K, form[c]);
-    if constexpr (SKIP) out[c] = free[c] ? __builtin_nan("") : out[c];
+    out[c] = interference_known(r, h[c], d[c], free[c], tab, K, form[c]);
   }
 }
 
@@ -430,16 +424,6 @@ __global__ __launch_bounds__(256) void k_pairs(EvalArgs a) {
 // Each wave keeps an LDS table of the 64 bucket minima of its current tile and writes it
 // as the tile's partials.
 // ---------------------------------------------------------------------------------------
-struct BucketEntry {
-  double edge;             // the bucket's upper memory edge E_j (+inf past NB - 1): the edge
-                           // and the key are adjacent, read together
-  unsigned long long key;  // bits of the minimum objective (a non-negative double orders like
-                           // its bit pattern)
-  unsigned int lid;        // lowest local id (id - group base, < 2^32) reaching it
-  unsigned int pad;
-};
-static_assert(sizeof(BucketEntry) == 24, "24-byte entries: the entry offset is one multiply-add");
-
 // Weight-sampled argmin (Eq. 4 with sampled alpha) of the wave's current tile: the value
 // (a double, for the fast comparison), its order key (for the LDS atomic minimum; weighted
 // values may be negative) and the lowest local id reaching it.
@@ -467,6 +451,11 @@ __device__ __forceinline__ T load_uniform(const T* p) {
 __device__ __forceinline__ unsigned long long order_key(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
   return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+
+// The double an order key stands for.
+__device__ __forceinline__ double order_value(unsigned long long k) {
+  return __longlong_as_double((long long)((k >> 63) ? k & 0x7FFFFFFFFFFFFFFFull : ~k));
 }
 
 // Orders this wave's LDS accesses for the compiler: a lane may read a word another lane of
@@ -508,6 +497,701 @@ __device__ __forceinline__ void pool_holes(const EvalArgs& a, unsigned long long
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// K1.  Bounded search: the results are minima (per bucket) or a filtered set (exact frontier), so
+// a part of the space whose lower bound on the objective is above what it would have to beat is
+// decided without forming its times.  A tile's strips are visited top down:
+//   - unit (pair, recomputed layers, ZeRO level; R^4 configurations), one lane each: bounds of the
+//     unit's memory and objective over all its ratios; live units' constants go to LDS records;
+//   - strip (weight and gradient ratio), one lane each, 64 at a time: the levels that the strip
+//     fixes, and bounds of its peak without the activation terms over the optimizer ratios;
+//   - column (activation ratio), the same for every lane: the memory range over the optimizer
+//     ratios and two lower bounds on the objective, before and after forming the stable time;
+//   - configuration (optimizer ratio): its own memory, bucket and bound, then, only when some lane
+//     of the wave may still win, Algorithm 1 and the reduction step.
+// Each test is wave-uniform (a ballot), so a level is skipped when it fails in every lane.
+//
+// The bounds.  Every slowdown factor is at least 1, so each stream's standalone time is progressed
+// by at most the phase length in every phase of Algorithm 1: a time it returns is at least each of
+// its streams' times.  With t >= tl and T1 >= T1l, obj = G t + (T1 - t) >= (G - 1) tl + T1l.  Host
+// streams grow with every ratio, so a level's smallest ones come with the smallest ratios still
+// open.  The memory without the activation terms is max(BF, BB), each a sum over the ratios of
+// functions that are linear in one ratio, so over the open ratios BF and BB lie between the sums of
+// their end values' minima and maxima, and the maximum of the two between the maximum of their lower
+// and that of their upper bounds.  Rounding: all terms are non-negative and a value takes a few
+// dozen operations of relative error 2^-53; the objective's bound is lowered by a relative 2^-30
+// (hw.lbs; with factors above 2^16, where T1 - t may cancel beyond that, it is lowered to 0 and
+// excludes nothing) and memory ranges are widened by a relative 2^-28.
+//
+// The thresholds.  In a bucket's minimum a configuration matters only if its objective is at most
+// the smallest known for its bucket (equal: the lowest id wins), so the test compares its bound with
+// the largest threshold among the buckets of its memory range (range_max).  A tile starts from its
+// group's thresholds so far (thr, filled by the seed variant below and lowered by every tile of the
+// group as it goes), each the objective of some configuration of that bucket: never below the
+// final minimum, so the winner itself is never excluded, whatever the order of the tiles.  In the
+// exact frontier's variant the threshold is pm, the least objective of the lower buckets, which
+// does not increase with the bucket: the lowest bucket of the range decides.
+// ---------------------------------------------------------------------------------------
+struct BucketEntry {
+  double edge;             // the bucket's upper memory edge E_j (+inf past NB - 1): the edge
+                           // and the key are adjacent, read together
+  unsigned long long key;  // bits of the minimum objective (a non-negative double orders like
+                           // its bit pattern)
+  unsigned int lid;        // lowest local id (id - group base, < 2^32) reaching it; 0xFFFFFFFF:
+                           // none of this tile
+  unsigned int pad;
+};
+static_assert(sizeof(BucketEntry) == 24, "24-byte entries: the entry offset is one multiply-add");
+
+// What a strip needs of its unit (pair, recomputed layers, ZeRO level).
+struct UnitRec {
+  double Sw, Sg, sw, sg;     // resident-if-kept weights and gradients, their shard factors
+  double Wb2, Obg, So, Obo;  // double-buffered fp16 unit, optimizer-step unit parts, optimizer states
+  double Rc, Xd;             // recompute unit, logits
+  double A, KA, A2;          // microbatch activations, in-flight stash, offload buffers
+  double C, gs, gf;          // compute, GPU-GPU stable and first microbatch
+  int32_t unit, pad;
+};
+static_assert(sizeof(UnitRec) == 136, "17 doubles: consecutive records start in different banks");
+
+constexpr int kUnits = 32;       // live unit records per wave
+constexpr int kRangeLevels = 7;  // range maxima over 1, 2, 4, .. 64 buckets
+
+// Largest of the thresholds of buckets a..b (0 <= a <= b <= 63): level e of tab holds the maxima over
+// [i, i + 2^e).
+__device__ __forceinline__ double range_max(const float* __restrict__ tab, unsigned int a, unsigned int b) {
+  const unsigned int e = 31u - (unsigned int)__builtin_clz(b - a + 1u);
+  const float* row = tab + e * 64u;
+  return (double)__builtin_fmaxf(row[a], row[b + 1u - (1u << e)]);
+}
+
+template <int R, int MODE>
+__global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* __restrict__ ratio,
+                                                      const PairK* __restrict__ pk) {
+  constexpr bool EX = MODE == kModeEmit;
+  constexpr bool DM = MODE == kModeDump;
+  constexpr bool SD = MODE == kModeSeed || MODE == kModeSeedAlpha;
+  constexpr bool AL = MODE == kModeAlpha || MODE == kModeSeedAlpha;
+  constexpr bool BK = MODE == kModeBuckets || SD || AL;
+  constexpr int R2 = R * R;
+  __shared__ double s_tab[kWaves][16 * kLdsRow + 2 * kTab2];
+  __shared__ BucketEntry s_bucket[kWaves][65];  // entries NB..64: sinks of infeasible configurations
+  __shared__ UnitRec s_unit[kWaves][kUnits];
+  __shared__ float s_range[BK ? kWaves : 1][BK ? kRangeLevels * 64 : 1];
+  __shared__ double s_ratio[2 * R];
+  __shared__ FiltEntry s_filt[EX ? kWaves : 1][EX ? 64 : 1];
+  __shared__ double2 s_ab[AL ? kWaves : 1][kMaxAlphas];      // alpha * G, 1 - alpha
+  __shared__ AlphaEntry s_aent[AL ? kWaves : 1][kMaxAlphas];
+  __shared__ double2 s_apq[AL ? kWaves : 1][kMaxAlphas];     // limits of d: P - Q t
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  // The wave index is uniform across the wave: stated, so that the tile, group and hardware
+  // values derived from it live in scalar registers (scalar loads) rather than in every lane.
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int NB = a.NB;
+  const double* __restrict__ rr = ratio;  // read-only and uniform: scalar loads
+  const double* __restrict__ om = ratio + R;
+  if (tid < 2 * R) s_ratio[tid] = ratio[tid];
+  __syncthreads();
+  const bool r0_zero = rr[0] == 0.0;
+  const double ra0 = rr[0], ra1 = rr[R - 1], qa0 = om[0], qa1 = om[R - 1];  // the end ratios
+  double* tab = s_tab[wave];
+  BucketEntry* bucket = s_bucket[wave];
+  float* range = s_range[BK ? wave : 0];
+  UnitRec* units = s_unit[wave];
+  const unsigned long long kEmpty = (unsigned long long)__double_as_longlong(__builtin_huge_val());
+
+  // Tile schedule: wave w of the grid takes work item w.  Item n_waves + x + kClaimCounters
+  // * c goes to the claim that draws number c from counter x (counters reset to 0 by K0); a
+  // wave draws from the counter of its block's XCD and moves to the next counter when one
+  // runs out, until all have.  When the grid has at least as many waves as there are items
+  // no claim is made.  Item x is tile tile_order[x] (the host gives each XCD's items a
+  // contiguous range of tiles), or tile tile_list[x] when a variant runs a list; the seed
+  // variant's items are the groups.
+  const bool listed = (EX || DM) && a.tile_list != nullptr;
+  const int n_items = SD ? (int)a.n_groups : (listed ? a.n_list : a.n_tiles);
+  const int n_waves = (int)gridDim.x * kWaves;
+  const bool claims = n_items > n_waves;
+  int counter = (int)(blockIdx.x % kClaimCounters);
+  int exhausted = 0;
+  int loaded_hw = -1;
+  // Exact frontier: the wave's current chunk of overflow-pool slots (none yet: used = chunk).
+  unsigned long long pool_base = 0;
+  int pool_used = kPoolChunk;
+  for (int x = (int)blockIdx.x * kWaves + wave; x < n_items;) {
+    const int t = SD ? 0 : (listed ? load_uniform(a.tile_list + x) : (a.tile_order ? load_uniform(a.tile_order + x) : x));
+    DevTile tile{x, 0, 0, 0};
+    if constexpr (!SD) tile = load_uniform(a.tiles + t);
+    // The exact frontier's pass skips a tile that holds no candidate (its count stays 0).
+    const int strip_end = EX && a.tile_live && !a.tile_live[t] ? tile.strip_begin : tile.strip_end;
+    const DevGroup g = load_uniform(a.groups + tile.group);
+    const DevHw& hw = a.hws[g.hw];
+    if (g.hw != loaded_hw) {  // the wave's LDS copy of the hardware tables
+      for (int i = lane; i < 16 * kTabStride; i += 64)
+        tab[(i / kTabStride) * kLdsRow + i % kTabStride] = (&hw.itab[0][0])[i];
+      wave_sync();
+      if (lane < 2 * kTab2) {  // the third round's rows of compute and one host stream, from the rows
+        const int h = 2 + lane / kTab2, i = lane % kTab2;
+        const int row = i < 4 ? (1 | (1 << h)) : 13;
+        const int col = ((i & 1) ? h : 0) + (i >= 2 ? 4 : 0);  // phi[0], phi[h], psi[0], psi[h], psi[0], psi[h]
+        tab[kTab2Off + lane] = tab[row * kLdsRow + col];
+      }
+      bucket[lane].edge = hw.edge[lane];
+      loaded_hw = g.hw;
+    }
+    // Buckets 0..NB-1 start empty.  Entries NB..64 are sinks: they hold key 0 and local id
+    // 0, which no configuration beats, so an infeasible configuration sent to one never
+    // takes part.
+    lds_store(&bucket[lane].key, lane < NB ? kEmpty : 0ull);
+    lds_store(&bucket[lane].lid, lane < NB ? 0xFFFFFFFFu : 0u);
+    if (lane == 0) {
+      bucket[64].edge = __builtin_huge_val();
+      bucket[64].key = 0ull;
+      bucket[64].lid = 0u;
+    }
+    const double Gd = (double)g.G;
+    const double Gm1 = Gd - 1.0;
+    int64_t n_cand = 0;  // exact frontier: the next candidate's slot
+    int64_t n_beg = 0;   // and the tile's window of slots
+    int64_t n_end = 0;
+    bool dropped = false;  // and whether a candidate of this lane found no place
+    if constexpr (EX) {
+      s_filt[wave][lane] = a.filt[(size_t)tile.group * 64 + lane];
+      n_beg = load_uniform(a.win_begin + t);  // wave-uniform: scalar registers
+      n_end = load_uniform(a.win_end + t);
+      n_cand = n_beg;
+    }
+    if constexpr (AL) {
+      if (lane < a.n_alpha) {
+        s_ab[wave][lane] = make_double2(a.alpha[lane] * Gd, a.beta[lane]);
+        lds_store(&s_aent[wave][lane].val, __builtin_huge_val());
+        lds_store(&s_aent[wave][lane].key, order_key(__builtin_huge_val()));
+        lds_store(&s_aent[wave][lane].lid, 0xFFFFFFFFu);
+      }
+    }
+    wave_sync();
+
+    const double iP = load_uniform(&hw.iP), kNB = load_uniform(&hw.kNB), M = load_uniform(&hw.M);
+    const double lbs = load_uniform(&hw.lbs);
+    [[maybe_unused]] const double slope0 = load_uniform(&hw.slope[0]), slope1 = load_uniform(&hw.slope[1]),
+                                  slope2 = load_uniform(&hw.slope[2]);
+    const double kLo = kNB * (1.0 - 0x1p-28), kHi = kNB * (1.0 + 0x1p-28), Mhi = M * (1.0 + 0x1p-28);
+    const RowK RK{load_uniform(&hw.itab[15][2]), load_uniform(&hw.itab[15][3]), load_uniform(&hw.itab[15][6]),
+                  load_uniform(&hw.itab[15][7]), load_uniform(&hw.itab[13][2]), load_uniform(&hw.itab[13][3])};
+    const int l = g.l;
+    const int64_t ke = g.k < g.G ? g.k : g.G;
+    unsigned long long* const thr = a.thr ? a.thr + (size_t)tile.group * 64 : nullptr;
+    unsigned long long* const athr = AL && a.athr ? a.athr + (size_t)tile.group * a.n_alpha : nullptr;
+
+    // The range maxima of the thresholds, each rounded up to the next float (at least the smallest
+    // normal one): still an upper bound.
+    auto build_range = [&](unsigned long long key) {
+      const unsigned int up = __float_as_uint((float)__longlong_as_double((long long)key));
+      unsigned int v = up >= 0x7F800000u ? 0x7F800000u : max(up + 1u, 0x00800000u);
+#pragma unroll
+      for (int e = 0; e < kRangeLevels; ++e) {
+        range[e * 64 + lane] = __uint_as_float(v);
+        v = max(v, (unsigned int)__shfl_down((int)v, 1u << e, 64));  // past lane 63: its own
+      }
+      wave_sync();
+    };
+    // Weight samples: with b = 1 - alpha > 0 a configuration matters to a sample only if
+    // d <= (v - alpha G t) / b with v the sample's smallest value known, a limit P - Q t of d given t.
+    // Q is lowered and P raised by a relative 2^-40 of their own magnitudes, far above the rounding
+    // of the limit and of the weighted value, in which the two may cancel.
+    [[maybe_unused]] auto build_alpha = [&]() {
+      if (lane < a.n_alpha) {
+        const double2 ab = s_ab[wave][lane];
+        const double v = lds_load(&s_aent[wave][lane].val);
+        const double ib = ab.y > 0.0 ? 1.0 / ab.y : 0.0;
+        double P = v * ib;
+        P = P + __builtin_fabs(P) * 0x1p-40;
+        s_apq[wave][lane] = ab.y > 0.0 ? make_double2(P, ab.x * ib * (1.0 - 0x1p-40)) : make_double2(v, -1.0);
+      }
+      wave_sync();
+    };
+    // The largest d with which a configuration of stable time t may matter to some sample.
+    [[maybe_unused]] auto d_limit = [&](double t) -> double {
+      double lim = -__builtin_huge_val();
+      for (int q = 0; q < a.n_alpha; ++q) {
+        const double2 pq = s_apq[wave][q];
+        if (pq.y < 0.0)  // alpha = 1: any d, if G t is small enough
+          lim = Gd * t * (1.0 - 0x1p-40) <= pq.x ? __builtin_huge_val() : lim;
+        else
+          lim = __builtin_fmax(lim, __builtin_fma(-pq.y, t, pq.x));
+      }
+      return lbs > 0.0 ? lim : __builtin_huge_val();
+    };
+    // Exchanges thresholds with the group's other tiles.  An entry that another tile holds lower
+    // takes that value with no local id: a configuration of this tile that reaches it later records
+    // its own.
+    auto exchange = [&](bool publish) {
+      wave_sync();
+      unsigned long long key = lds_load(&bucket[lane].key);
+      if (thr && !SD && lane < NB) {
+        const unsigned long long cur = __hip_atomic_load(thr + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cur < key) {
+          lds_store(&bucket[lane].key, cur);
+          lds_store(&bucket[lane].lid, 0xFFFFFFFFu);
+          key = cur;
+        } else if (publish && key < cur) {
+          __hip_atomic_fetch_min(thr + lane, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+      build_range(key);
+      if constexpr (AL) {
+        if (lane < a.n_alpha) {
+          AlphaEntry* const e = &s_aent[wave][lane];
+          const unsigned long long mine = lds_load(&e->key);
+          if (athr && !SD) {
+            const unsigned long long cur = __hip_atomic_load(athr + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (cur < mine) {
+              lds_store(&e->key, cur);
+              lds_store(&e->val, order_value(cur));
+              lds_store(&e->lid, 0xFFFFFFFFu);
+            } else if (publish && mine < cur) {
+              __hip_atomic_fetch_min(athr + lane, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+          }
+        }
+        build_alpha();
+      }
+    };
+    // The largest objective that a configuration in the memory range [lo, hi] may have to matter.
+    auto limit = [&](double lo, double hi) -> double {
+      const unsigned int ja = (unsigned int)__builtin_fmin(lo * kLo, 63.0);
+      if constexpr (EX) {
+        return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(s_filt[wave]) +
+                                                __umul24(ja, (unsigned int)sizeof(FiltEntry)));
+      } else if constexpr (BK) {
+        const unsigned int jb = (unsigned int)__builtin_fmin(hi * kHi, 63.0);
+        return range_max(range, ja, max(ja, jb));
+      } else {
+        return __builtin_huge_val();
+      }
+    };
+    // Whether something of memory at least lo and objective bound lb can matter below limit th.
+    auto alive = [&](double lo, double lb, double th) -> bool {
+      if constexpr (DM) return true;
+      if constexpr (EX) return (lo <= Mhi) & (lb * lbs < th);
+      return (lo <= Mhi) & (lb * lbs <= th);
+    };
+
+    // Whether something with t >= tl and T1 >= T1l can matter to some weight sample: for
+    // alpha G >= 1 - alpha the value (alpha G - (1 - alpha)) t + (1 - alpha) T1 grows with both, for
+    // the others it needs t itself.
+    [[maybe_unused]] auto sample_alive = [&](double tl, double T1l) -> bool {
+      bool may = !(lbs > 0.0);
+      for (int q = 0; q < a.n_alpha; ++q) {
+        const double2 ab = s_ab[wave][q];
+        const double v = lds_load(&s_aent[wave][q].val);
+        may = may | (ab.x < ab.y) | (__builtin_fma(ab.x - ab.y, tl, ab.y * T1l) * lbs <= v);
+      }
+      return may;
+    };
+
+    const int nu = g.n_pairs * (l + 1) * 4;  // units of the group
+    // The tile's units in chunks of kUnits, one lane each.  A chunk takes one unit of each of kUnits
+    // equal segments, so that the first ones sample the whole tile and the thresholds settle early;
+    // the place within the segment turns with the lane, which mixes the ZeRO levels.  The seed
+    // variant samples one chunk over the whole group.
+    const int u_beg = tile.strip_begin / R2;
+    const int n_u = SD ? nu : (strip_end > tile.strip_begin ? (strip_end - 1) / R2 + 1 - u_beg : 0);
+    const int n_chunks = (n_u + kUnits - 1) / kUnits;
+    for (int k = 0; k < (SD ? 1 : n_chunks); ++k) {
+      if constexpr (BK) exchange(k > 0);
+      const int at = (k + lane) % n_chunks + n_chunks * lane;
+      const int u = u_beg + at;
+      bool live = lane < kUnits && at < n_u;
+      UnitRec rec{};
+      if (live) {
+        const int uc = u >> 2, z = u & 3;
+        const int p = uc / (l + 1);
+        const int c = uc - p * (l + 1);
+        const PairK P = pk[g.pk_begin + p];
+        const CkptK K = ckpt_level(P, l, c, ke);
+        const ZeroK Z = zero_level(P, z);
+        rec = UnitRec{Z.Sw, Z.Sg, Z.sw, Z.sg, P.Wb2, Z.Obg, Z.So, Z.Obo, K.Rc, P.Xd,
+                      K.A, K.KA, P.A2, K.C, Z.G2Gs, Z.G2Gf, u, 0};
+        if constexpr (!DM && !SD) {
+          // End values of each ratio's terms: weights (both peaks), gradients and optimizer states
+          // (forward peak, backward peak), activations.
+          const double w0 = qa0 * Z.Sw + P.Wb2 * (1.0 - qa0 * Z.sw), w1 = qa1 * Z.Sw + P.Wb2 * (1.0 - qa1 * Z.sw);
+          const double gf0 = qa0 * Z.Sg + ra0 * Z.Obg, gf1 = qa1 * Z.Sg + ra1 * Z.Obg;
+          const double gb0 = qa0 * Z.Sg + P.Wb2 * (1.0 - qa0 * Z.sg), gb1 = qa1 * Z.Sg + P.Wb2 * (1.0 - qa1 * Z.sg);
+          const double of0 = qa0 * Z.So + ra0 * Z.Obo, of1 = qa1 * Z.So + ra1 * Z.Obo;
+          const double ob0 = qa0 * Z.So, ob1 = qa1 * Z.So;
+          const double s0 = ra0 * P.A2 + qa0 * K.KA, s1 = ra1 * P.A2 + qa1 * K.KA;
+          const double wl = __builtin_fmin(w0, w1), wh = __builtin_fmax(w0, w1);
+          const double lo = __builtin_fmax(wl + __builtin_fmin(gf0, gf1) + __builtin_fmin(of0, of1),
+                                           wl + __builtin_fmin(gb0, gb1) + ob1 + K.Rc) + P.Xd + __builtin_fmin(s0, s1);
+          const double hi = __builtin_fmax(wh + __builtin_fmax(gf0, gf1) + __builtin_fmax(of0, of1),
+                                           wh + __builtin_fmax(gb0, gb1) + ob0 + K.Rc) + P.Xd + __builtin_fmax(s0, s1);
+          const double hl = ra0 * (K.A + 2.0 * Z.Sw) * iP, dl = ra0 * (K.A + Z.Sg) * iP;
+          const double tl = __builtin_fmax(__builtin_fmax(K.C, Z.G2Gs), __builtin_fmax(hl, dl));
+          const double T1l = __builtin_fmax(__builtin_fmax(K.C, Z.G2Gf),
+                                            __builtin_fmax(hl + ra0 * (Z.So + Z.Sg) * iP, dl + ra0 * (Z.So + Z.Sw) * iP));
+          live = alive(lo, __builtin_fma(Gm1, tl, T1l), limit(lo, hi));
+          if constexpr (AL) live = live | ((lo <= Mhi) & sample_alive(tl, T1l));
+        }
+      }
+      const unsigned long long lm = __builtin_amdgcn_ballot_w64(live);
+      const int n_live = __builtin_popcountll(lm);
+      wave_sync();  // the previous units' records are done with
+      if (live)
+        units[__builtin_amdgcn_mbcnt_hi((unsigned int)(lm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)lm, 0u))] = rec;
+      wave_sync();
+
+      // Strips of the live units, one lane each, 64 at a time.
+      const int n_strips = SD ? 64 * kSeedIters : n_live * R2;
+      bool changed = false;  // some bucket's minimum fell since the range maxima were formed
+      for (int i0 = 0; i0 < n_strips; i0 += 64) {
+        if (BK && changed) {
+          wave_sync();
+          build_range(lds_load(&bucket[lane].key));
+          if constexpr (AL) build_alpha();
+          changed = false;
+        }
+        const int i = i0 + lane;
+        int slot, rem2;
+        bool on;
+        if constexpr (SD) {  // two lanes per unit
+          slot = lane >> 1;
+          on = slot < n_live;
+          rem2 = (lane & 1) ? (int)((unsigned int)(lane * 37 + (i0 >> 6) * 29) % (unsigned int)R2) : (i0 >> 6) % R2;
+        } else {
+          slot = i / R2;
+          rem2 = i - slot * R2;
+          on = i < n_strips;
+        }
+        slot = on ? slot : 0;
+        const UnitRec& U = units[slot];
+        const int s = U.unit * R2 + rem2;
+        if constexpr (!SD) on = on & (s >= tile.strip_begin) & (s < strip_end);
+        const int iw = rem2 / R;
+        const int ig = rem2 - iw * R;
+        const double rw = s_ratio[iw], qw = s_ratio[R + iw], rg = s_ratio[ig], qg = s_ratio[R + ig];
+        const double So = U.So, Obo = U.Obo, Rc = U.Rc, Xd = U.Xd;
+        const double Wbuf = U.Wb2 * (1.0 - qw * U.sw);
+        const double Swg = __builtin_fma(qg, U.Sg, qw * U.Sw);
+        const double Gbuf = U.Wb2 * (1.0 - qg * U.sg);
+        const double HW = rw * (2.0 * U.Sw), DW = rw * U.Sw, DG = rg * U.Sg, Og = rg * U.Obg;
+        const double A = U.A, KA = U.KA, A2 = U.A2, C = U.C, gs = U.gs, gf = U.gf;
+        const OoIn I{So, Swg, Obo, Og, DG, DW, Wbuf, Gbuf, Rc, Xd};
+        // Peak without the activation terms over the optimizer ratios: between Blo and Bhi.
+        double Blo, Bhi;
+        {
+          const double b0 = __builtin_fma(qa0, So, Swg) + Wbuf, b1 = __builtin_fma(qa1, So, Swg) + Wbuf;
+          const double f0 = b0 + __builtin_fma(ra0, Obo, Og), f1 = b1 + __builtin_fma(ra1, Obo, Og);
+          const double g0 = (b0 + Gbuf) + Rc, g1 = (b1 + Gbuf) + Rc;
+          Blo = __builtin_fmax(__builtin_fmin(f0, f1), g1) + Xd;
+          Bhi = __builtin_fmax(__builtin_fmax(f0, f1), g0) + Xd;
+        }
+        const double Hx0 = __builtin_fma(ra0, So, DG) * iP, Dx0 = __builtin_fma(ra0, So, DW) * iP;
+        const double tc = __builtin_fmax(C, gs), T1c = __builtin_fmax(C, gf);
+        const bool zero_strip = r0_zero && rw == 0.0 && rg == 0.0;
+        const unsigned int lid_strip = (unsigned int)s * (unsigned int)R2;
+        // Both calls' first rounds.  With a positive activation ratio both host streams run, so the
+        // stable microbatch's first round has the pattern compute, both host streams, and GPU-GPU
+        // when it carries traffic; the first microbatch's configurations with a non-zero offload
+        // ratio start likewise.
+        const KnownRow sr = known_row(tab, gs > 0.0 ? 15 : 13, C, gs);
+        const KnownRow fr = known_row(tab, gf > 0.0 ? 15 : 13, C, gf);
+        // Weight samples: whether the strip may matter to one, the largest d with which it may, and
+        // whether it may matter to a bucket (few strips do: the others' columns skip that test).
+        [[maybe_unused]] bool smp = false, bkt = true;
+        [[maybe_unused]] double dls = 0.0;
+        if constexpr (AL) {
+          const double hl = __builtin_fma(ra0, A, HW) * iP, dl = __builtin_fma(ra0, A, DG) * iP;
+          const double tl = __builtin_fmax(tc, __builtin_fmax(hl, dl));
+          const double T1l = __builtin_fmax(T1c, __builtin_fmax(hl + Hx0, dl + Dx0));
+          const double s0 = __builtin_fma(ra0, A2, qa0 * KA), s1 = __builtin_fma(ra1, A2, qa1 * KA);
+          const double lo = Blo + __builtin_fmin(s0, s1), hi = Bhi + __builtin_fmax(s0, s1);
+          on = on & (lo <= Mhi);
+          smp = sample_alive(tl, T1l);
+          bkt = __builtin_amdgcn_ballot_w64(on & alive(lo, __builtin_fma(Gm1, tl, T1l), limit(lo, hi))) != 0ull;
+          if (!bkt & !__builtin_amdgcn_ballot_w64(on & smp)) continue;
+          dls = d_limit(tl * lbs);
+        }
+
+#pragma unroll 1
+        for (int ia = 0; ia < R; ++ia) {
+          const double ra = rr[ia], qa = om[ia];
+          const double hs = __builtin_fma(ra, A, HW) * iP;
+          const double ds = __builtin_fma(ra, A, DG) * iP;
+          const double SO = __builtin_fma(ra, A2, qa * KA);  // stash + offload buffers
+          const double T1l = __builtin_fmax(T1c, __builtin_fmax(hs + Hx0, ds + Dx0));
+          bool col = false;  // matters to a bucket (or the exact frontier)
+          double th = 0.0;
+          if (!AL || bkt) {
+            th = limit(Blo + SO, Bhi + SO);
+            col = on & alive(Blo + SO, __builtin_fma(Gm1, __builtin_fmax(tc, __builtin_fmax(hs, ds)), T1l), th);
+          }
+          [[maybe_unused]] bool acol = false;  // matters to a weight sample
+          if constexpr (AL) acol = on & (Blo + SO <= Mhi) & smp;
+          if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
+          // The stable time does not depend on the optimizer ratio.
+          double tv;
+          [[maybe_unused]] int fst = kFormGeneric;
+          if (ia == 0 && r0_zero)
+            tv = interference(C, gs, hs, ds, tab);
+          else
+            tv = interference_known(sr, hs, ds, !(col | acol), tab, RK, fst);
+          col = col & alive(Blo + SO, __builtin_fma(Gm1, tv, T1l), th);
+          if constexpr (AL) acol = acol & (__builtin_fma(T1l, lbs, -tv) <= dls);
+          if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
+          // Weight samples: the column's first-microbatch time T10 at the smallest optimizer ratio
+          // bounds the others'.  Each is that time with both host streams longer by the same
+          // (r - r0) So / PCIe, and Algorithm 1's time is continuous and piecewise linear in that
+          // length, with no slope below slope0 (slope1 when GPU-GPU finishes first at the smallest
+          // ratio, slope2 when compute follows: as the host streams grow, it stays so).  With a
+          // negative slope the bound falls until it meets the host streams, which grow with slope 1.
+          // (For the buckets alone it excludes too little for its cost: 6.4 against 5.7 ms on
+          // llama42b-d128-hw64.)
+          [[maybe_unused]] double T10 = 0.0, sl = 0.0, dl = 0.0;
+          if constexpr (AL) {
+            int f0 = kFormGeneral;
+            const double h0 = hs + Hx0, d0 = ds + Dx0;
+            if (ia == 0)
+              T10 = interference(C, gf, h0, d0, tab);
+            else
+              T10 = interference_known(fr, h0, d0, !(col | acol), tab, RK, f0);
+            sl = f0 == kFormGeneral ? slope0 : (f0 == kFormHostsLeft ? slope2 : slope1);
+            const double neg = __builtin_fmin(sl, 0.0);
+            const double T1m = __builtin_fmax(T1l, T10 + neg * (1.0 / (1.0 - neg)) * (T10 - __builtin_fmax(h0, d0)));
+            col = col & alive(Blo + SO, __builtin_fma(Gm1, tv, T1m), th);
+            acol = acol & (__builtin_fma(T1m, lbs, -tv) <= dls);
+            if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
+            dl = d_limit(tv);
+            acol = acol & (__builtin_fma(T1m, lbs, -tv) <= dl);
+            if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
+          }
+
+#pragma unroll 1
+          for (int io = 0; io < R; ++io) {
+            const OoK O = oo_level(I, rr[io], om[io], iP);
+            const double hf = hs + O.H2Dx, df = ds + O.D2Hx;
+            const double mem = O.Bmax + SO;
+            // Bucket j = min{j : mem <= E_j}: floor(mem * kNB) is j or j - 1 (kNB carries a
+            // 2^-40 margin), so one comparison with E settles it.  An infeasible
+            // configuration (Eq. 4: mem > M = E_{NB-1}) has floor(mem * kNB) >= NB - 1 and
+            // lands on a sink: past NB - 1 the edges are +inf.  j0 = j - 1 needs mem within a
+            // relative 2^-40 above an edge, or an infeasible mem just above M: rare, so only
+            // entry j0's edge and key are read, and entry j0 + 1 (<= 64: entry 64's edge is
+            // +inf) only by lanes whose mem exceeds E_j0.
+            const int j0 = (int)__builtin_fmin(mem * kNB, 64.0);
+            const unsigned int off0 = __umul24((unsigned int)j0, (unsigned int)sizeof(BucketEntry));
+            char* const b0 = reinterpret_cast<char*>(bucket) + off0;
+            wave_sync();  // read the entry after every earlier update of the wave
+            const double e0 = reinterpret_cast<const BucketEntry*>(b0)->edge;
+            const unsigned long long k_lo = lds_load(&reinterpret_cast<const BucketEntry*>(b0)->key);
+            const bool up = mem > e0;
+            // The configuration's own bound against its bucket (a lane in entry j0 + 1 is kept).
+            bool may = col;
+            double T1b = __builtin_fmax(T1c, __builtin_fmax(hf, df));
+            if constexpr (AL) T1b = __builtin_fmax(T1b, __builtin_fma(sl, O.H2Dx - Hx0, T10));
+            const double lb = __builtin_fma(Gm1, tv, T1b);
+            [[maybe_unused]] bool amay = false;
+            if constexpr (EX) {
+              const double pm = *reinterpret_cast<const double*>(
+                  reinterpret_cast<const char*>(s_filt[wave]) + __umul24((unsigned int)min(j0, 63), (unsigned int)sizeof(FiltEntry)));
+              may = may & (mem <= M) & (lb * lbs < pm);
+            } else if constexpr (BK) {
+              may = may & ((lb * lbs <= __longlong_as_double((long long)k_lo)) | up);
+              if constexpr (AL) {
+                amay = acol & (mem <= M) & (__builtin_fma(T1b, lbs, -tv) <= dl);
+                may = may | amay;
+              }
+            }
+            if (!__builtin_amdgcn_ballot_w64(may)) continue;
+            [[maybe_unused]] int f1 = 0;
+            const bool zero = ia == 0 && io == 0 && zero_strip;
+            double T1 = interference_known(fr, hf, df, !may | zero, tab, RK, f1);
+            if (ia == 0 && io == 0) {  // the strip's all-zero configuration: no host streams
+              const double T1z = interference_zero(C, gf, tab);
+              T1 = zero ? T1z : T1;
+            }
+            const double d = T1 - tv;
+            const double obj = __builtin_fma(Gd, tv, d);
+            const unsigned int lid = lid_strip + (unsigned int)(io * R + ia);
+            if constexpr (DM) {
+              if (on) {
+                double* o = a.dump + kDumpWords * (a.dump_off[x] + (int64_t)(s - tile.strip_begin) * R2 + io * R + ia);
+                o[0] = tv;
+                o[1] = d;
+                o[2] = mem;
+                o[3] = obj;
+                o[4] = (double)(j0 + (up ? 1 : 0));
+                o[5] = (double)((zero ? kFormZero : f1) + 8 * fst);
+              }
+              continue;
+            }
+            if constexpr (EX) {
+              // Exact frontier candidates: feasible, below every lower bucket's minimum, and not
+              // dominated by the bucket's winner (no more memory and no smaller objective, not
+              // both equal).  Every frontier point passes; the scan after the sort decides.
+              const int j = min(j0 + (up ? 1 : 0), 63);
+              const FiltEntry f = s_filt[wave][j];
+              const bool cand = may & (obj < f.pm) &
+                                !(((obj > f.bobj) & (mem >= f.bmem)) | ((obj >= f.bobj) & (mem > f.bmem)));
+              const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
+              if (!m) continue;
+              int64_t slot = 0;
+              if (cand) {
+                const unsigned int below = __builtin_amdgcn_mbcnt_hi(
+                    (unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+                slot = n_cand + below;
+                if (slot < n_end) {
+                  a.cand_key[slot] = (unsigned long long)__double_as_longlong(mem);
+                  a.cand_obj[slot] = obj;
+                  a.cand_id[slot] = g.base + (uint64_t)lid;
+                }
+              }
+              // Past the window: the overflow pool, in chunks of kPoolChunk slots per wave (one
+              // device-wide atomic per chunk), else counted only and the tile is evaluated again.
+              const bool over = cand && slot >= n_end;
+              const unsigned long long mo = __builtin_amdgcn_ballot_w64(over);
+              if (mo && a.pool_count) {
+                const int k = __builtin_popcountll(mo);
+                if (pool_used + k > kPoolChunk) {
+                  pool_holes(a, pool_base, pool_used, lane);
+                  const int leader = __builtin_ctzll(mo);
+                  unsigned long long b = 0;
+                  if (lane == leader) b = atomicAdd(a.pool_count, (unsigned long long)kPoolChunk);
+                  const unsigned long long bb = __shfl(b, leader, 64);
+                  pool_base = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)(bb >> 32)) << 32) |
+                              (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)bb);
+                  pool_used = 0;
+                }
+                if (over) {
+                  const unsigned long long pos = pool_base + (unsigned long long)pool_used + __builtin_amdgcn_mbcnt_hi(
+                      (unsigned int)(mo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mo, 0u));
+                  if (pos < (unsigned long long)a.pool_cap) {
+                    a.pool_key[pos] = (unsigned long long)__double_as_longlong(mem);
+                    a.pool_obj[pos] = obj;
+                    a.pool_id[pos] = g.base + (uint64_t)lid;
+                    a.pool_tile[pos] = t;
+                    a.pool_rank[pos] = (int32_t)(slot - n_beg);
+                  } else {
+                    dropped = true;
+                  }
+                }
+                pool_used += k;
+              } else if (mo) {
+                dropped = dropped | over;
+              }
+              n_cand += __builtin_popcountll(m);
+              continue;
+            }
+
+            // Lexicographic (obj, id) minimum per bucket without a serial loop: the lanes
+            // that beat their bucket's entry lower the objective bits with an LDS atomic
+            // minimum; a lane that sees its bucket's objective drop clears the id, then the
+            // lanes whose objective equals the new minimum lower the id.  The LDS operations
+            // of a wave execute in program order and each step addresses the same words as
+            // the one before, so each step sees the previous one's result.
+            const unsigned long long key = (unsigned long long)__double_as_longlong(obj);
+            if (__builtin_amdgcn_ballot_w64(may & ((key <= k_lo) | up))) {
+              BucketEntry* const be = reinterpret_cast<BucketEntry*>(b0 + (up ? sizeof(BucketEntry) : 0));
+              const unsigned long long k_old = up ? lds_load(&be->key) : k_lo;
+              const unsigned int i_old = lds_load(&be->lid);
+              const bool cand = may & ((key < k_old) | ((key == k_old) & (lid < i_old)));
+              changed = changed | (__builtin_amdgcn_ballot_w64(cand) != 0ull);
+              if (cand) atomicMin(&be->key, key);
+              const unsigned long long k_new = cand ? lds_load(&be->key) : 0ull;
+              if (cand && k_new < k_old) lds_store(&be->lid, 0xFFFFFFFFu);
+              if (cand && key == k_new) atomicMin(&be->lid, lid);
+            }
+            if constexpr (AL) {
+              // Eq. 4 for every weight sample, feasible configurations only: the samples some lane
+              // may win, each with the same three-step sequence on its single entry (the value's
+              // order key: weighted values may be negative).
+              amay = amay & (d <= dl);
+              if (__builtin_amdgcn_ballot_w64(amay)) {
+#pragma unroll 1
+                for (int q = 0; q < a.n_alpha; ++q) {
+                  const double2 ab = s_ab[wave][q];
+                  AlphaEntry* const e = &s_aent[wave][q];
+                  const double v = __builtin_fma(ab.x, tv, ab.y * d);
+                  const double cur = lds_load(&e->val);
+                  if (!__builtin_amdgcn_ballot_w64(amay & (v <= cur))) continue;
+                  const unsigned long long ak = order_key(v);
+                  const unsigned long long ak_old = lds_load(&e->key);
+                  const unsigned int ai_old = lds_load(&e->lid);
+                  const bool cand = amay & ((ak < ak_old) | ((ak == ak_old) & (lid < ai_old)));
+                  changed = changed | (__builtin_amdgcn_ballot_w64(cand) != 0ull);
+                  if (cand) atomicMin(&e->key, ak);
+                  const unsigned long long ak_new = cand ? lds_load(&e->key) : 0ull;
+                  if (cand && ak_new < ak_old) lds_store(&e->lid, 0xFFFFFFFFu);
+                  if (cand && ak == ak_new) {
+                    atomicMin(&e->lid, lid);
+                    lds_store(&e->val, v);
+                  }
+                  wave_sync();
+                }
+              }
+            }
+          }
+        }
+      }
+    }
+    if constexpr (SD) {
+      // The group's first thresholds: objectives of configurations of each bucket.
+      wave_sync();
+      thr[lane] = lds_load(&bucket[lane].key);
+      if constexpr (AL)
+        if (lane < a.n_alpha) athr[lane] = lds_load(&s_aent[wave][lane].key);
+    } else if constexpr (EX) {
+      // Saturated at 2^31 - 1, which the host rejects (no tile of a space with fewer than
+      // 2^32 candidates reaches it).
+      if (lane == 0) a.cnt_tile[t] = (int32_t)min(n_cand - n_beg, (int64_t)0x7FFFFFFF);
+      const unsigned long long md = __builtin_amdgcn_ballot_w64(dropped);
+      if (lane == 0 && a.tile_drop) a.tile_drop[t] = md ? 1 : 0;
+    } else if constexpr (!DM) {
+      // The tile's partials: lane j = bucket j.  A bucket that no configuration of this tile
+      // reached carries the threshold it did not beat (the tile's configurations of that bucket, if
+      // any, have larger objectives) and no id.
+      wave_sync();
+      const unsigned long long key = lds_load(&bucket[lane].key);
+      const unsigned int bl = lds_load(&bucket[lane].lid);
+      if (thr && lane < NB && bl != 0xFFFFFFFFu)
+        __hip_atomic_fetch_min(thr + lane, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      a.part_obj[(size_t)t * 64 + lane] = __longlong_as_double((long long)key);
+      a.part_id[(size_t)t * 64 + lane] = bl == 0xFFFFFFFFu ? kNone : g.base + (uint64_t)bl;
+      if constexpr (AL) {
+        if (lane < a.n_alpha) {
+          const unsigned long long ak = lds_load(&s_aent[wave][lane].key);
+          const unsigned int al = lds_load(&s_aent[wave][lane].lid);
+          if (athr && al != 0xFFFFFFFFu)
+            __hip_atomic_fetch_min(athr + lane, ak, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          a.part_aobj[(size_t)t * a.n_alpha + lane] = order_value(ak);
+          a.part_aid[(size_t)t * a.n_alpha + lane] = al == 0xFFFFFFFFu ? kNone : g.base + (uint64_t)al;
+        }
+      }
+    }
+    if (!claims) break;
+    for (;;) {
+      int c = 0;
+      if (lane == 0) c = atomicAdd(a.work + counter * kCounterStride, 1);
+      c = __builtin_amdgcn_readfirstlane(__shfl(c, 0, 64));
+      const int64_t next = (int64_t)n_waves + counter + (int64_t)kClaimCounters * c;
+      if (next < n_items) {
+        x = (int)next;
+        break;
+      }
+      if (++exhausted == kClaimCounters) {  // every counter has run out: no item is left
+        x = n_items;
+        break;
+      }
+      counter = counter + 1 == kClaimCounters ? 0 : counter + 1;
+    }
+  }
+  if constexpr (EX) {
+    if (a.pool_count) pool_holes(a, pool_base, pool_used, lane);
+  }
+}
+
 // Activation ratios per block of the strip loop: a block keeps its stable times and the
 // per-ratio terms of its configurations in registers across the optimizer ratios.
 // Weight samples take larger blocks for 7 <= R <= 10 (at R = 9, 79.5 against 85.2 ms for 8
@@ -517,45 +1201,26 @@ constexpr int ia_block() {
   return R <= 6 ? R : (MODE == kModeAlpha && R <= 10 ? (R + 1) / 2 : (R + 2) / 3);
 }
 
-// A value every lane of the wave holds, moved to scalar registers.
-__device__ __forceinline__ double wave_uniform(double x) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)b);
-  const unsigned int hi = __builtin_amdgcn_readfirstlane((unsigned int)(b >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 // Waves per SIMD the register allocation aims at: four, 128 registers per lane (a few
 // strip-level values spill; the occupancy is worth more).  Five would fit the LDS of the blocks,
-// but at 96 registers the inner loop spills: 77 against 59 ms on the 64-sample Llama space.  The
-// exact frontier's candidate variant keeps more per configuration live; with a whole strip's
-// activation ratios in one block (R <= 6) three waves and fewer spills are faster (1.60 against
-// 1.83 ms for the exact frontier on gpt2.7b-d16), with larger R four.
-template <int R, int MODE>
-constexpr int eval_waves() { return MODE == kModeEmit && R <= 6 ? 3 : 4; }
+// but at 96 registers the inner loop spills: 77 against 59 ms on the 64-sample Llama space.
+constexpr int kEvalWaves = 4;
 
 // MODE kModeBuckets: bucket minima; kModeAlpha: also the weight-sampled argmins of Eq. 4
-// (a.n_alpha samples); kModeEmit: the exact frontier's candidates, written and counted per
-// tile (the bucket reduction is skipped).
+// (a.n_alpha samples); kModeDump: per-configuration values of listed tiles.
 template <int R, int MODE>
-__global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalArgs a, const double* __restrict__ ratio,
+__global__ __launch_bounds__(kBlock, kEvalWaves) void k_eval(EvalArgs a, const double* __restrict__ ratio,
                                                                  const PairK* __restrict__ pk) {
   constexpr bool AL = MODE == kModeAlpha;
-  constexpr bool EX = MODE == kModeEmit;
   constexpr bool DM = MODE == kModeDump;
   constexpr int R2 = R * R;
   constexpr int SU = 4 * R2;  // strips per (pair, c) unit
   constexpr int IB = ia_block<R, MODE>();
-  // Exact frontier with the activation ratios in several blocks: lower bounds per strip and per
-  // block (below).  With the whole strip in one block the candidates are dense and the bounds
-  // rarely hold for a whole wave (1 % of the wave iterations on gpt2.7b-d16, simulated).
-  constexpr bool BLK = EX && IB < R;
   __shared__ double s_tab[kWaves][16 * kLdsRow + 2 * kTab2];
   __shared__ BucketEntry s_bucket[kWaves][65];  // entries NB..64: sinks of infeasible configurations
   __shared__ OoIn s_oo[kBlock];         // per-lane strip constants of the optimizer level
   __shared__ double2 s_ab[AL ? kWaves : 1][kMaxAlphas];      // alpha * G, 1 - alpha
   __shared__ AlphaEntry s_aent[AL ? kWaves : 1][kMaxAlphas];
-  __shared__ FiltEntry s_filt[EX ? kWaves : 1][EX ? 64 : 1];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -566,18 +1231,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
   const double* __restrict__ rr = ratio;  // read-only and uniform: scalar loads
   const double* __restrict__ om = ratio + R;
   const bool r0_zero = rr[0] == 0.0;
-  // The smallest offload ratio and the smallest 1 - r, for the strip bounds.
-  [[maybe_unused]] double r_lo = 0.0, q_lo = 0.0;
-  if constexpr (BLK) {
-    r_lo = rr[0];
-    q_lo = om[0];
-    for (int i = 1; i < R; ++i) {
-      r_lo = __builtin_fmin(r_lo, rr[i]);
-      q_lo = __builtin_fmin(q_lo, om[i]);
-    }
-    r_lo = wave_uniform(r_lo);
-    q_lo = wave_uniform(q_lo);
-  }
   double* tab = s_tab[wave];
   BucketEntry* bucket = s_bucket[wave];
   const unsigned long long kEmpty = (unsigned long long)__double_as_longlong(__builtin_huge_val());
@@ -588,21 +1241,16 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
   // runs out, until all have.  When the grid has at least as many waves as there are items
   // no claim is made.  Item x is tile tile_order[x] (the host gives each XCD's items a
   // contiguous range of tiles), or tile tile_list[x] when a variant runs a list.
-  const bool listed = (EX || DM) && a.tile_list != nullptr;
+  const bool listed = DM && a.tile_list != nullptr;
   const int n_items = listed ? a.n_list : a.n_tiles;
   const int n_waves = (int)gridDim.x * kWaves;
   const bool claims = n_items > n_waves;
   int counter = (int)(blockIdx.x % kClaimCounters);
   int exhausted = 0;
   int loaded_hw = -1;
-  // Exact frontier: the wave's current chunk of overflow-pool slots (none yet: used = chunk).
-  unsigned long long pool_base = 0;
-  int pool_used = kPoolChunk;
   for (int x = (int)blockIdx.x * kWaves + wave; x < n_items;) {
     const int t = listed ? load_uniform(a.tile_list + x) : (a.tile_order ? load_uniform(a.tile_order + x) : x);
     const DevTile tile = load_uniform(a.tiles + t);
-    // The exact frontier's pass skips a tile that holds no candidate (its count stays 0).
-    const int strip_end = EX && a.tile_live && !a.tile_live[t] ? tile.strip_begin : tile.strip_end;
     const DevGroup g = load_uniform(a.groups + tile.group);
     const DevHw& hw = a.hws[g.hw];
     if (g.hw != loaded_hw) {  // the wave's LDS copy of the hardware tables
@@ -629,16 +1277,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
       bucket[64].lid = 0u;
     }
     const double Gd = (double)g.G;
-    int64_t n_cand = 0;  // exact frontier: the next candidate's slot
-    int64_t n_beg = 0;   // and the tile's window of slots
-    int64_t n_end = 0;
-    bool dropped = false;  // and whether a candidate of this lane found no place
-    if constexpr (EX) {
-      s_filt[wave][lane] = a.filt[(size_t)tile.group * 64 + lane];
-      n_beg = load_uniform(a.win_begin + t);  // wave-uniform: scalar registers
-      n_end = load_uniform(a.win_end + t);
-      n_cand = n_beg;
-    }
     if constexpr (AL) {
       if (lane < a.n_alpha) {
         s_ab[wave][lane] = make_double2(a.alpha[lane] * Gd, a.beta[lane]);
@@ -656,7 +1294,7 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
     const int64_t ke = g.k < g.G ? g.k : g.G;
 
 #pragma unroll 1
-    for (int s = tile.strip_begin + lane; s < strip_end; s += 64) {
+    for (int s = tile.strip_begin + lane; s < tile.strip_end; s += 64) {
       const int unit = s / SU;
       const int rem = s - unit * SU;
       const int z = rem / R2;
@@ -670,40 +1308,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
       const ZeroK Z = zero_level(P, z);
       const double rw = rr[iw], rg = rr[ig];
       const WoGoK W = wogo_levels(P, Z, rw, om[iw], rg, om[ig]);
-      // Exact frontier: lower bounds of the optimizer level's peak and first-microbatch extras over
-      // the strip's optimizer ratios, then a first candidate bound for the whole strip.  Every
-      // input of the level is non-negative, so each of its operations is non-decreasing in the
-      // ratio r or in 1 - r; the bounds repeat the level's own operations on the smallest r and
-      // the smallest 1 - r (the resident states shrink with r, the offloaded states' buffer and
-      // the extras grow with it), and rounding to nearest is monotone: each is at most the value
-      // of every optimizer ratio, the peak's as max(forward, backward) of two lower bounds.
-      [[maybe_unused]] double Bmin = 0.0, Hxmin = 0.0, Dxmin = 0.0;
-      if constexpr (BLK) {
-        const double base = __builtin_fma(q_lo, Z.So, W.Swg) + W.Wbuf;
-        const double BF = (base + __builtin_fma(r_lo, Z.Obo, W.Og)) + P.Xd;
-        const double BB = ((base + W.Gbuf) + K.Rc) + P.Xd;
-        Bmin = __builtin_fmax(BF, BB);
-        Hxmin = __builtin_fma(r_lo, Z.So, W.DG) * iP;
-        Dxmin = __builtin_fma(r_lo, Z.So, W.DW) * iP;
-        {
-          // The strip bound, before the stable times: with every slowdown factor at least 1 a
-          // stable time is at least each of its streams' times (compute, GPU-GPU and the host
-          // streams, whose smallest values come with the smallest activation ratio), and the
-          // stash and offload buffers are at least fma(r_lo, 2A, q_lo * KA).  The bound is the
-          // block bound below with those values in place of the block's own, so it is at most
-          // every configuration's; a strip that fails in every lane of the wave is skipped whole
-          // (the relative 2^-30 covers the rounding of the stable time as well).
-          const double hsl = __builtin_fma(r_lo, K.A, W.HW) * iP, dsl = __builtin_fma(r_lo, K.A, W.DG) * iP;
-          const double mem = Bmin + __builtin_fma(r_lo, P.A2, q_lo * K.KA);
-          const unsigned int j0 = (unsigned int)__builtin_fmin(mem * kNB, 63.0);
-          const double pm = *reinterpret_cast<const double*>(
-              reinterpret_cast<const char*>(s_filt[wave]) + __umul24(j0, (unsigned int)sizeof(FiltEntry)));
-          const double tl = __builtin_fmax(__builtin_fmax(K.C, Z.G2Gs), __builtin_fmax(hsl, dsl));
-          const double lb = __builtin_fma(Gd - 1.0, tl, __builtin_fmax(hsl + Hxmin, dsl + Dxmin));
-          if (!__builtin_amdgcn_ballot_w64((mem <= M) & (lb * (1.0 - 0x1p-30) < pm))) continue;
-        }
-      }
-
       // First microbatch: every configuration of the strip with a non-zero offload ratio
       // starts with compute, both host streams and (if it carries traffic) GPU-GPU.
       const int pat1 = Z.G2Gf > 0.0 ? 15 : 13;
@@ -713,8 +1317,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
       const double T1z = interference_zero(K.C, Z.G2Gf, tab);
       s_oo[tid] = oo_inputs(P, K, Z, W);
       const double A = K.A, KA = K.KA, A2 = P.A2, HW = W.HW, DG = W.DG;
-      // Block bound: the strip's smallest optimizer-level peak and first-microbatch extras over
-      // the optimizer ratios, each the minimum of the values the configurations use.
       const unsigned int lid_strip = (unsigned int)s * (unsigned int)R2;
       // With a positive activation ratio both host streams run, so the stable microbatch's
       // first round has the pattern compute + both host streams (+ GPU-GPU when it carries
@@ -733,7 +1335,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
         const KnownRow sr = known_row(tab, pats, K.C, Z.G2Gs);
         double tt[IB];
         [[maybe_unused]] int fst[IB];  // dump variant: the form of each stable time
-        [[maybe_unused]] double hsmin = 0.0, dsmin = 0.0;  // block bound: the smallest host streams
         {
           double hs[IB], ds[IB];
           bool fs[IB];
@@ -746,16 +1347,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
             fs[c] = ia == 0 && r0_zero;
           }
           interference_known_n<IB>(sr, hs, ds, fs, tt, fst, nb, tab, RK);
-          if constexpr (BLK) {
-            hsmin = hs[0];
-            dsmin = ds[0];
-#pragma unroll
-            for (int c = 1; c < IB; ++c) {
-              if (ib + c >= R) break;
-              hsmin = __builtin_fmin(hsmin, hs[c]);
-              dsmin = __builtin_fmin(dsmin, ds[c]);
-            }
-          }
           // Activation ratio 0 leaves the host streams to the weights and gradients alone: the
           // first round's pattern is not known in advance.
           if (ib == 0 && r0_zero) {
@@ -769,32 +1360,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
 #pragma unroll
           for (int c = 1; c < IB; ++c)
             if (ib + c < R) t_min = __builtin_fmin(t_min, tt[c]);
-        }
-
-        if constexpr (BLK) {
-          // Exact frontier: the candidate bound of the configurations below, taken once for the
-          // block.  Each of its terms is at most, over the block's optimizer and activation
-          // ratios, the value a configuration's bound uses (its memory from the peak's bound and
-          // the smallest stash, its host streams from the smallest stable parts and the extras'
-          // bounds, the smallest stable time); rounding is monotone, so the block's memory,
-          // bucket estimate and bound are at most each configuration's, and its threshold pm at
-          // least each one's (pm does not increase with the bucket).  A block that fails in every lane of the wave holds no
-          // configuration that passes its own bound, and none that can be a candidate: the
-          // strip's all-zero configuration, whose time is formed without the bound, has host
-          // streams 0 and so an objective of at least (G - 1) t as well.
-          double tmin = tt[0], somin = __builtin_fma(rr[ib], A2, om[ib] * KA);
-#pragma unroll
-          for (int c = 1; c < IB; ++c) {
-            if (ib + c >= R) break;
-            tmin = __builtin_fmin(tmin, tt[c]);
-            somin = __builtin_fmin(somin, __builtin_fma(rr[ib + c], A2, om[ib + c] * KA));
-          }
-          const double mem = Bmin + somin;
-          const unsigned int j0 = (unsigned int)__builtin_fmin(mem * kNB, 63.0);
-          const double pm = *reinterpret_cast<const double*>(
-              reinterpret_cast<const char*>(s_filt[wave]) + __umul24(j0, (unsigned int)sizeof(FiltEntry)));
-          const double lb = __builtin_fma(Gd - 1.0, tmin, __builtin_fmax(hsmin + Hxmin, dsmin + Dxmin));
-          if (!__builtin_amdgcn_ballot_w64((mem <= M) & (lb * (1.0 - 0x1p-30) < pm))) continue;
         }
 
 #pragma unroll 1
@@ -816,30 +1381,8 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
               hf[c] = __builtin_fma(rr[ia], A, HW) * iP + O.H2Dx;
               df[c] = __builtin_fma(rr[ia], A, DG) * iP + O.D2Hx;
               fz[c] = ia == 0 && zero_oo;
-              if constexpr (EX) {
-                // The exact frontier's candidates are feasible and below every lower bucket's
-                // minimum pm of their bucket; a configuration that fails either needs no
-                // first-microbatch time (its candidate test fails).  With every slowdown factor
-                // at least 1 each stream's standalone time is progressed by at most the phase
-                // length in every round, so T1 is at least every stream's time, in particular
-                // max(H2D, D2H), and obj = G t + (T1 - t) >= (G - 1) t + max(H2D, D2H); the
-                // bound is lowered by a relative 2^-30, far above the rounding of either side (a
-                // few dozen operations of relative error 2^-53), so a configuration whose bound
-                // is not below pm cannot be a candidate.  (Compute and GPU-GPU would tighten it
-                // little and cost registers: 92 against 72 bytes of scratch, same time.)  pm does
-                // not increase with the bucket (a prefix minimum), so the estimate
-                // j0 = floor(mem * kNB) <= j of the bucket step serves: pm[j0] >= pm[j].
-                const double mem = O.Bmax + __builtin_fma(rr[ia], A2, om[ia] * KA);
-                const unsigned int j0 = (unsigned int)__builtin_fmin(mem * kNB, 63.0);
-                const double pm = *reinterpret_cast<const double*>(
-                    reinterpret_cast<const char*>(s_filt[wave]) + __umul24(j0, (unsigned int)sizeof(FiltEntry)));
-                const double lb = __builtin_fma(Gd - 1.0, tt[c], __builtin_fmax(hf[c], df[c]));
-                // Such a lane takes no part in the choice of form; its T1, and so its objective,
-                // is NaN, which fails the candidate test.
-                fz[c] = fz[c] | !((mem <= M) & (lb * (1.0 - 0x1p-30) < pm));
-              }
             }
-            interference_known_n<IB, EX>(fr, hf, df, fz, T1b, f1b, nb, tab, RK);
+            interference_known_n<IB>(fr, hf, df, fz, T1b, f1b, nb, tab, RK);
           }
 #pragma unroll
           for (int c = 0; c < IB; ++c) {
@@ -850,11 +1393,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
             const double mem = O.Bmax + SO;
             double T1 = T1b[c];
             if (ia == 0) T1 = zero_oo ? T1z : T1;
-            // Exact frontier: a lane whose time was not formed (NaN) cannot hold a candidate, and
-            // when no lane of the wave has a time the configuration is done.
-            if constexpr (EX) {
-              if (!__builtin_amdgcn_ballot_w64(T1 == T1)) continue;
-            }
             const double tv = tt[c];
             const double d = T1 - tv;
             const double obj = __builtin_fma(Gd, tv, d);
@@ -880,63 +1418,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
               o[3] = obj;
               o[4] = (double)(j0 + (mem > e0 ? 1 : 0));
               o[5] = (double)((ia == 0 && zero_oo ? kFormZero : f1b[c]) + 8 * fst[c]);
-              continue;
-            }
-            if constexpr (EX) {
-              // Exact frontier candidates: feasible, below every lower bucket's minimum, and not
-              // dominated by the bucket's winner (no more memory and no smaller objective, not
-              // both equal).  Every frontier point passes; the scan after the sort decides.
-              const int j = min(j0 + (mem > e0 ? 1 : 0), 63);
-              const FiltEntry f = s_filt[wave][j];
-              const bool cand = (mem <= M) & (obj < f.pm) &
-                                !(((obj > f.bobj) & (mem >= f.bmem)) | ((obj >= f.bobj) & (mem > f.bmem)));
-              const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
-              if (!m) continue;
-              int64_t slot = 0;
-              if (cand) {
-                const unsigned int below = __builtin_amdgcn_mbcnt_hi(
-                    (unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
-                slot = n_cand + below;
-                if (slot < n_end) {
-                  a.cand_key[slot] = (unsigned long long)__double_as_longlong(mem);
-                  a.cand_obj[slot] = obj;
-                  a.cand_id[slot] = g.base + (uint64_t)(lid_oo + (unsigned int)ia);
-                }
-              }
-              // Past the window: the overflow pool, in chunks of kPoolChunk slots per wave (one
-              // device-wide atomic per chunk), else counted only and the tile is evaluated again.
-              const bool over = cand && slot >= n_end;
-              const unsigned long long mo = __builtin_amdgcn_ballot_w64(over);
-              if (mo && a.pool_count) {
-                const int k = __builtin_popcountll(mo);
-                if (pool_used + k > kPoolChunk) {
-                  pool_holes(a, pool_base, pool_used, lane);
-                  const int leader = __builtin_ctzll(mo);
-                  unsigned long long b = 0;
-                  if (lane == leader) b = atomicAdd(a.pool_count, (unsigned long long)kPoolChunk);
-                  const unsigned long long bb = __shfl(b, leader, 64);
-                  pool_base = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)(bb >> 32)) << 32) |
-                              (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)bb);
-                  pool_used = 0;
-                }
-                if (over) {
-                  const unsigned long long pos = pool_base + (unsigned long long)pool_used + __builtin_amdgcn_mbcnt_hi(
-                      (unsigned int)(mo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mo, 0u));
-                  if (pos < (unsigned long long)a.pool_cap) {
-                    a.pool_key[pos] = (unsigned long long)__double_as_longlong(mem);
-                    a.pool_obj[pos] = obj;
-                    a.pool_id[pos] = g.base + (uint64_t)(lid_oo + (unsigned int)ia);
-                    a.pool_tile[pos] = t;
-                    a.pool_rank[pos] = (int32_t)(slot - n_beg);
-                  } else {
-                    dropped = true;
-                  }
-                }
-                pool_used += k;
-              } else if (mo) {
-                dropped = dropped | over;
-              }
-              n_cand += __builtin_popcountll(m);
               continue;
             }
             const bool up = mem > e0;
@@ -1039,20 +1520,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
     }
     // The tile's partials: lane j = bucket j.
     if constexpr (DM) {
-    } else if constexpr (EX) {
-      // The wave's pool chunk is updated inside the strip loop, which lanes past a ragged
-      // tile's last strip leave early: lane 0 stays to the end and holds the current chunk.
-      {
-        const unsigned long long b = __shfl(pool_base, 0, 64);
-        pool_base = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)(b >> 32)) << 32) |
-                    (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)b);
-        pool_used = __builtin_amdgcn_readfirstlane(__shfl(pool_used, 0, 64));
-      }
-      // Saturated at 2^31 - 1, which the host rejects (no tile of a space with fewer than
-      // 2^32 candidates reaches it).
-      if (lane == 0) a.cnt_tile[t] = (int32_t)min(n_cand - n_beg, (int64_t)0x7FFFFFFF);
-      const unsigned long long md = __builtin_amdgcn_ballot_w64(dropped);
-      if (lane == 0 && a.tile_drop) a.tile_drop[t] = md ? 1 : 0;
     } else {
       wave_sync();
       const unsigned int bl = bucket[lane].lid;
@@ -1082,9 +1549,6 @@ __global__ __launch_bounds__(kBlock, (eval_waves<R, MODE>())) void k_eval(EvalAr
       }
       counter = counter + 1 == kClaimCounters ? 0 : counter + 1;
     }
-  }
-  if constexpr (EX) {
-    if (a.pool_count) pool_holes(a, pool_base, pool_used, lane);
   }
 }
 
@@ -1321,9 +1785,18 @@ int check_launch() {
   return e == hipSuccess ? 0 : (int)e;
 }
 
+// The exact frontier and the seeds run in the bounded search only.
+constexpr bool search_only(int mode) { return mode == kModeEmit || mode == kModeSeed || mode == kModeSeedAlpha; }
+
 template <int R, int MODE>
 void launch_eval_rm(const EvalArgs& a, int blocks, hipStream_t st) {
-  hipLaunchKernelGGL((k_eval<R, MODE>), dim3(blocks), dim3(kBlock), 0, st, a, a.ratio, (const PairK*)a.pk);
+  if constexpr (!search_only(MODE)) {
+    if (!a.bounded) {
+      hipLaunchKernelGGL((k_eval<R, MODE>), dim3(blocks), dim3(kBlock), 0, st, a, a.ratio, (const PairK*)a.pk);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_search<R, MODE>), dim3(blocks), dim3(kBlock), 0, st, a, a.ratio, (const PairK*)a.pk);
 }
 
 template <int R>
@@ -1332,23 +1805,27 @@ void launch_eval_r(const EvalArgs& a, int blocks, int mode, hipStream_t st) {
     case kModeAlpha: launch_eval_rm<R, kModeAlpha>(a, blocks, st); break;
     case kModeEmit: launch_eval_rm<R, kModeEmit>(a, blocks, st); break;
     case kModeDump: launch_eval_rm<R, kModeDump>(a, blocks, st); break;
+    case kModeSeed: launch_eval_rm<R, kModeSeed>(a, blocks, st); break;
+    case kModeSeedAlpha: launch_eval_rm<R, kModeSeedAlpha>(a, blocks, st); break;
     default: launch_eval_rm<R, kModeBuckets>(a, blocks, st); break;
   }
 }
 
 template <int R, int MODE>
-int blocks_per_cu_rm() {
+int blocks_per_cu_rm(bool bounded) {
   int n = 0;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_eval<R, MODE>, kBlock, 0) == hipSuccess ? n : 1;
+  if constexpr (!search_only(MODE))
+    if (!bounded) return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_eval<R, MODE>, kBlock, 0) == hipSuccess ? n : 1;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_search<R, MODE>, kBlock, 0) == hipSuccess ? n : 1;
 }
 
 template <int R>
-int blocks_per_cu_r(int mode) {
+int blocks_per_cu_r(int mode, bool bounded) {
   switch (mode) {
-    case kModeAlpha: return blocks_per_cu_rm<R, kModeAlpha>();
-    case kModeEmit: return blocks_per_cu_rm<R, kModeEmit>();
-    case kModeDump: return blocks_per_cu_rm<R, kModeDump>();
-    default: return blocks_per_cu_rm<R, kModeBuckets>();
+    case kModeAlpha: return blocks_per_cu_rm<R, kModeAlpha>(bounded);
+    case kModeEmit: return blocks_per_cu_rm<R, kModeEmit>(bounded);
+    case kModeDump: return blocks_per_cu_rm<R, kModeDump>(bounded);
+    default: return blocks_per_cu_rm<R, kModeBuckets>(bounded);
   }
 }
 
@@ -1357,11 +1834,11 @@ int blocks_per_cu_r(int mode) {
 
 }  // namespace
 
-int eval_blocks_per_cu(int R, int mode) {
+int eval_blocks_per_cu(int R, int mode, bool bounded) {
   switch (R) {
 #define MIST_CASE(n) \
   case n:            \
-    return blocks_per_cu_r<n>(mode);
+    return blocks_per_cu_r<n>(mode, bounded);
     MIST_FOR_EACH_R(MIST_CASE)
 #undef MIST_CASE
     default:
