@@ -147,12 +147,15 @@ struct mist_space {
   bool exact_done = false;
   bool exact_launched = false;  // some call enqueued uploads of the host offset tables
   hipStream_t exact_stream = nullptr;
+  std::vector<DevTile> cand_tiles;  // tiles of the candidate pass (build_cand_tiles)
+  std::vector<int32_t> cand_first;  // and the first one of each group, then their count
+  DevTile* d_cand_tiles = nullptr;
   FiltEntry* d_filt = nullptr;
   int32_t* d_cnt_tile = nullptr;
   int64_t* d_tile_off = nullptr;
   int64_t* d_tile_end = nullptr;
   int32_t* d_list = nullptr;
-  uint8_t* d_live = nullptr;  // per tile: may hold a candidate
+  uint8_t* d_live = nullptr;  // per tile: some unit may hold a candidate
   // Overflow pool of the candidate pass: candidates past their tile's window.
   unsigned long long* d_pool_count = nullptr;
   int64_t pool_cap = 0;
@@ -536,7 +539,6 @@ mist::EvalArgs eval_args(const mist_space* S) {
   a.ratio = S->d_ratio;
   a.R = S->R;
   a.NB = S->NB;
-  a.bounded = S->bounded ? 1 : 0;
   a.n_tiles = (int32_t)S->tiles.size();
   a.n_groups = (int64_t)S->groups.size();
   a.n_configs = S->n_configs;
@@ -666,6 +668,24 @@ bool use_bounds(const mist_space* S) {
   return g > 0 && n >= kBoundedConfigs && n / g >= kBoundedPerGroup;
 }
 
+uint64_t align_strips(uint64_t v) {
+  v = (v + kStripAlign - 1) / kStripAlign * kStripAlign;
+  if (v < (uint64_t)kStripAlign) v = kStripAlign;
+  if (v > (uint64_t)INT32_MAX / 2) v = (uint64_t)INT32_MAX / 2 / kStripAlign * kStripAlign;
+  return v;
+}
+
+// Strips of a full-size tile (see build_tiles); *single when every wave takes one tile.
+uint64_t tile_strips(const mist_space* S, uint64_t total_strips, int64_t resident_waves, bool bounded, bool* single) {
+  const uint64_t W = (uint64_t)std::max<int64_t>(1, resident_waves);
+  const uint64_t R2 = (uint64_t)(S->R * S->R);
+  *single = !bounded && total_strips <= W * (uint64_t)kStaticStrips;
+  if (*single) return align_strips((total_strips + W - 1) / W);
+  uint64_t spt = ((uint64_t)(S->tile_configs > 0 ? S->tile_configs : bounded ? kMinBoundedConfigs : kMinTileConfigs) + R2 - 1) / R2;
+  if (bounded && S->tile_configs == 0) spt = std::max<uint64_t>(spt, total_strips / (W * kTilesPerWave));
+  return align_strips(std::max<uint64_t>(spt, (total_strips + (uint64_t)kMaxTiles - 1) / (uint64_t)kMaxTiles));
+}
+
 // Tiles: contiguous strips of one group, at most strips_per_tile each (a multiple of the wave
 // width).  Every wave of the persistent evaluation grid takes tile number (its global wave
 // index) first and claims further tiles from the device counter, in tile order.  A space of
@@ -680,25 +700,9 @@ std::string build_tiles(mist_space* S, int64_t resident_waves) {
   const uint64_t per_unit_strips = 4ull * (uint64_t)(S->R * S->R);
   uint64_t total_strips = 0;
   for (const DevGroup& g : S->groups) total_strips += (uint64_t)g.n_pairs * (uint64_t)(g.l + 1) * per_unit_strips;
-  const uint64_t W = (uint64_t)std::max<int64_t>(1, resident_waves);
-  const uint64_t R2 = (uint64_t)(S->R * S->R);
-  const auto align = [](uint64_t v) {
-    v = (v + kStripAlign - 1) / kStripAlign * kStripAlign;
-    if (v < (uint64_t)kStripAlign) v = kStripAlign;
-    if (v > (uint64_t)INT32_MAX / 2) v = (uint64_t)INT32_MAX / 2 / kStripAlign * kStripAlign;
-    return v;
-  };
-  const bool single = !S->bounded && total_strips <= W * (uint64_t)kStaticStrips;
-  uint64_t spt;
-  if (single)
-    spt = align((total_strips + W - 1) / W);
-  else
-    spt = align(std::max<uint64_t>(S->tile_configs > 0 ? ((uint64_t)S->tile_configs + R2 - 1) / R2
-                               : S->bounded ? std::max<uint64_t>(((uint64_t)kMinBoundedConfigs + R2 - 1) / R2,
-                                                                 total_strips / (W * kTilesPerWave))
-                                            : ((uint64_t)kMinTileConfigs + R2 - 1) / R2,
-                                   (total_strips + (uint64_t)kMaxTiles - 1) / (uint64_t)kMaxTiles));
-  const uint64_t spt_tail = single ? spt : align(spt / 4);
+  bool single = false;
+  const uint64_t spt = tile_strips(S, total_strips, resident_waves, S->bounded, &single);
+  const uint64_t spt_tail = single ? spt : align_strips(spt / 4);
   S->strips_per_tile = (int32_t)spt;
   S->tiles.clear();
   std::vector<DevTile> tail;
@@ -730,6 +734,32 @@ std::string build_tiles(mist_space* S, int64_t resident_waves) {
   for (DevGroup& g : S->groups) g.tail_begin += full;
   S->tiles.insert(S->tiles.end(), tail.begin(), tail.end());
   return "";
+}
+
+// Tiles of the exact frontier's candidate pass, in group order.  Its thresholds are final before it
+// starts, so small tiles cost nothing there and balance better than the bounded search's (llama7b-d32:
+// 3.3 ms for the whole exact frontier against 4.2).
+void build_cand_tiles(mist_space* S, int64_t resident_waves) {
+  const uint64_t per_unit_strips = 4ull * (uint64_t)(S->R * S->R);
+  uint64_t total = 0;
+  for (const DevGroup& g : S->groups) total += (uint64_t)g.n_pairs * (uint64_t)(g.l + 1) * per_unit_strips;
+  bool single = false;
+  const int64_t spt = (int64_t)tile_strips(S, total, resident_waves, false, &single);
+  S->cand_tiles.clear();
+  S->cand_first.clear();
+  for (size_t gi = 0; gi < S->groups.size(); ++gi) {
+    const DevGroup& g = S->groups[gi];
+    const int64_t strips = (int64_t)g.n_pairs * (g.l + 1) * (int64_t)per_unit_strips;
+    S->cand_first.push_back((int32_t)S->cand_tiles.size());
+    for (int64_t u = 0; u < strips; u += spt) {
+      DevTile t{};
+      t.group = (int32_t)gi;
+      t.strip_begin = (int32_t)u;
+      t.strip_end = (int32_t)std::min<int64_t>(strips, u + spt);
+      S->cand_tiles.push_back(t);
+    }
+  }
+  S->cand_first.push_back((int32_t)S->cand_tiles.size());
 }
 
 // Work items of the persistent evaluation grid in tile order per XCD.  Item i < n_waves is the
@@ -824,7 +854,8 @@ mist_status mist_space_create(const mist_model_desc* m, const mist_hw_desc* hw, 
       hipError_t e = hipGetDevice(&dev);
       if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
       if (e != hipSuccess) rc = fail_hip(e, "device attributes");
-      const int per_cu = eval_blocks_per_cu(S->R, S->A > 0 ? kModeAlpha : kModeBuckets, S->bounded);
+      const int mode = S->A > 0 ? kModeAlpha : kModeBuckets;
+      const int per_cu = S->bounded ? search_blocks_per_cu(S->R, mode) : eval_blocks_per_cu(S->R, mode);
       resident_blocks = std::max<int64_t>(1, (int64_t)cus * (per_cu > 0 ? per_cu : 1));
       if (S->max_blocks > 0) resident_blocks = std::min<int64_t>(resident_blocks, S->max_blocks);
       S->cus = cus;
@@ -936,10 +967,11 @@ mist_status mist_eval_space(mist_space* S, void* hip_stream) {
     if (e != hipSuccess) return fail_hip(e, "hipEventRecord");
   }
   if (ea.thr) {
-    rc = launch_eval(ea, (int)((ea.n_groups + kWaves - 1) / kWaves), S->A > 0 ? kModeSeedAlpha : kModeSeed, st);
+    rc = launch_search(ea, (int)((ea.n_groups + kWaves - 1) / kWaves), S->A > 0 ? kModeSeedAlpha : kModeSeed, st);
     if (rc) return fail_hip((hipError_t)rc, "seed kernel launch");
   }
-  rc = launch_eval(ea, S->eval_grid, S->A > 0 ? kModeAlpha : kModeBuckets, st);
+  const int mode = S->A > 0 ? kModeAlpha : kModeBuckets;
+  rc = S->bounded ? launch_search(ea, S->eval_grid, mode, st) : launch_eval(ea, S->eval_grid, mode, st);
   if (rc) return fail_hip((hipError_t)rc, "evaluation kernel launch");
   if (ev) {
     const hipError_t e = hipEventRecord(ev[1], st);
@@ -974,13 +1006,16 @@ mist_status mist_eval_space(mist_space* S, void* hip_stream) {
   return MIST_OK;
 }
 
-// Grid of the persistent evaluation kernel in a given variant.
-static int32_t mode_grid(const mist_space* S, int mode) {
-  const int per_cu = eval_blocks_per_cu(S->R, mode, S->bounded);
-  int64_t resident = std::max<int64_t>(1, (int64_t)S->cus * (per_cu > 0 ? per_cu : 1));
-  if (S->max_blocks > 0) resident = std::min<int64_t>(resident, S->max_blocks);
-  const int64_t waves_needed = (int64_t)(S->tiles.size() + kWaves - 1) / kWaves;
-  return (int32_t)std::max<int64_t>(1, std::min<int64_t>(resident, waves_needed));
+// Blocks of a variant of the evaluation kernel that are resident at once, and its persistent grid over
+// n tiles.
+static int64_t resident_blocks(const mist_space* S, int mode) {
+  const int per_cu = S->bounded || mode == kModeEmit ? search_blocks_per_cu(S->R, mode) : eval_blocks_per_cu(S->R, mode);
+  const int64_t resident = std::max<int64_t>(1, (int64_t)S->cus * (per_cu > 0 ? per_cu : 1));
+  return S->max_blocks > 0 ? std::min<int64_t>(resident, S->max_blocks) : resident;
+}
+
+static int32_t mode_grid(const mist_space* S, int mode, size_t n) {
+  return (int32_t)std::max<int64_t>(1, std::min<int64_t>(resident_blocks(S, mode), (int64_t)(n + kWaves - 1) / kWaves));
 }
 
 mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
@@ -989,7 +1024,8 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
   if (rc) return rc;
   try {
     hipStream_t st = (hipStream_t)hip_stream;
-    const size_t nt = S->tiles.size(), ng = S->groups.size();
+    if (S->cand_first.empty()) build_cand_tiles(S, resident_blocks(S, kModeEmit) * kWaves);
+    const size_t nt = S->cand_tiles.size(), ng = S->groups.size();
     // The host offset tables below are uploaded asynchronously: a previous call on another
     // stream must be done with them before they are rewritten.
     if (S->exact_launched && S->exact_stream != st) {
@@ -1002,7 +1038,7 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
       const int64_t R2 = (int64_t)S->R * S->R;
       auto slots = [&](int64_t div) {
         int64_t n = 0;
-        for (const DevTile& T : S->tiles) n += ((int64_t)(T.strip_end - T.strip_begin) * R2 + div - 1) / div;
+        for (const DevTile& T : S->cand_tiles) n += ((int64_t)(T.strip_end - T.strip_begin) * R2 + div - 1) / div;
         return n;
       };
       int64_t div = S->cand_window > 0 ? S->cand_window : kWindowDiv;
@@ -1010,11 +1046,12 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
         while (slots(div) > kWindowSlots) div *= 2;
       S->h_slab_begin.assign(nt + 1, 0);
       for (size_t t = 0; t < nt; ++t) {
-        const DevTile& T = S->tiles[t];
+        const DevTile& T = S->cand_tiles[t];
         S->h_slab_begin[t + 1] = S->h_slab_begin[t] + ((int64_t)(T.strip_end - T.strip_begin) * R2 + div - 1) / div;
       }
       const size_t n_slab = (size_t)std::max<int64_t>(S->h_slab_begin[nt], 1);
       S->d_filt = (FiltEntry*)dev_alloc(S, std::max<size_t>(ng, 1) * 64 * sizeof(FiltEntry), st);
+      S->d_cand_tiles = (DevTile*)dev_alloc(S, std::max<size_t>(nt, 1) * sizeof(DevTile), st);
       S->d_cnt_tile = (int32_t*)dev_alloc(S, std::max<size_t>(nt, 1) * sizeof(int32_t), st);
       S->d_tile_off = (int64_t*)dev_alloc(S, std::max<size_t>(nt, 1) * sizeof(int64_t), st);
       S->d_tile_end = (int64_t*)dev_alloc(S, std::max<size_t>(nt, 1) * sizeof(int64_t), st);
@@ -1054,7 +1091,7 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
           S->h_drop = (uint8_t*)(S->h_pool_count + 1);
         }
       }
-      void** bufs[] = {(void**)&S->d_filt,      (void**)&S->d_cnt_tile,   (void**)&S->d_tile_off,
+      void** bufs[] = {(void**)&S->d_filt,      (void**)&S->d_cand_tiles, (void**)&S->d_cnt_tile,   (void**)&S->d_tile_off,
                        (void**)&S->d_tile_end,  (void**)&S->d_list,       (void**)&S->d_seg, (void**)&S->d_seg_end, (void**)&S->d_live,
                        (void**)&S->d_front_cnt, (void**)&S->d_slab_begin, (void**)&S->d_slab_key,
                        (void**)&S->d_slab_obj,  (void**)&S->d_slab_id,    (void**)&S->d_pool_count,
@@ -1071,12 +1108,17 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
         S->h_pinned = nullptr;
         return fail(MIST_E_NOMEM, "device allocation failed: exact frontier");
       }
-      const hipError_t e = copy_sync(S->d_slab_begin, S->h_slab_begin.data(), (nt + 1) * sizeof(int64_t),
-                                     hipMemcpyHostToDevice);
+      hipError_t e = copy_sync(S->d_slab_begin, S->h_slab_begin.data(), (nt + 1) * sizeof(int64_t),
+                               hipMemcpyHostToDevice);
+      if (e == hipSuccess)
+        e = copy_sync(S->d_cand_tiles, S->cand_tiles.data(), nt * sizeof(DevTile), hipMemcpyHostToDevice);
       if (e != hipSuccess) return fail_hip(e, "exact frontier: windows");
     }
     // Pass 1: every tile writes its candidates to its window and counts them.
     EvalArgs ea = eval_args(S);
+    ea.tiles = S->d_cand_tiles;
+    ea.tile_order = nullptr;
+    ea.n_tiles = (int32_t)nt;
     ea.filt = S->d_filt;
     ea.cnt_tile = S->d_cnt_tile;
     ea.win_begin = S->d_slab_begin;
@@ -1096,9 +1138,8 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
     ea.pool_rank = S->d_pool_rank;
     ea.tile_drop = S->d_tile_drop;
     int k = launch_filter(ea, S->d_bucket_obj, S->d_bucket_id, S->d_filt, st);
-    if (!k) k = launch_live(ea, S->d_filt, S->d_live, st);
     if (!k) k = launch_pairs(ea, st);  // also resets the tile counters and the pool
-    if (!k) k = launch_eval(ea, mode_grid(S, kModeEmit), kModeEmit, st);
+    if (!k) k = launch_search(ea, mode_grid(S, kModeEmit, nt), kModeEmit, st);
     if (k) return fail_hip((hipError_t)k, "exact frontier: candidates");
     hipError_t e = copy_async(S->h_cnt, S->d_cnt_tile, nt * sizeof(int32_t), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = copy_async(S->h_drop, S->d_tile_drop, nt, hipMemcpyDeviceToHost, st);
@@ -1109,7 +1150,7 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
     // tile: neither that kernel nor the candidate pass runs, the counter keeps whatever its
     // block held, and the pool is empty.
     const int64_t n_pool = ea.n_pk > 0 ? std::min<int64_t>((int64_t)*S->h_pool_count, S->pool_cap) : 0;
-    // Candidate slots in group order: a group's full-size tiles, then its small ones.  Tiles with
+    // Candidate slots in group order.  Tiles with
     // a candidate that found no place (its window and the pool full) are listed for pass 2.
     S->n_list = 0;
     int64_t off = 0;
@@ -1122,10 +1163,8 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
       if (S->h_drop[t]) S->h_list[S->n_list++] = t;
     };
     for (size_t g = 0; g < ng; ++g) {
-      const DevGroup& G = S->groups[g];
       S->h_seg[g] = off;
-      for (int32_t t = G.tile_begin; t < G.tile_begin + G.n_tiles; ++t) place(t);
-      for (int32_t t = G.tail_begin; t < G.tail_begin + G.n_tail; ++t) place(t);
+      for (int32_t t = S->cand_first[g]; t < S->cand_first[g + 1]; ++t) place(t);
     }
     S->h_seg[ng] = off;
     if (off >= ((int64_t)1 << 32)) return fail(MIST_E_RANGE, "exact frontier: more than 2^32 candidates");
@@ -1179,7 +1218,7 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
       ea.cand_obj = S->d_cand_obj;
       ea.cand_id = S->d_cand_id;
       k = launch_pairs(ea, st);
-      if (!k) k = launch_eval(ea, mode_grid(S, kModeEmit), kModeEmit, st);
+      if (!k) k = launch_search(ea, mode_grid(S, kModeEmit, nt), kModeEmit, st);
     }
     if (!k) k = launch_prefilter(S->d_cand_key, S->d_cand_obj, S->d_cand_id, S->d_seg, (int64_t)ng, S->d_seg_end, st);
     // The frontier's key array and the slot array d_idx_in serve as the sort's scratch (the scan
@@ -1215,7 +1254,7 @@ mist_status mist_exact_info(mist_space* S, int64_t* n_candidates, int64_t* n_kep
     if (e != hipSuccess) return fail_hip(e, "hipMemcpy segment ends");
     int64_t kept = 0;
     for (size_t g = 0; g < ng; ++g) kept += ends[g] - S->h_seg[g];
-    const size_t nt = S->tiles.size();
+    const size_t nt = S->cand_tiles.size();
     std::vector<uint8_t> live(nt);
     e = copy_sync(live.data(), S->d_live, nt, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpy live tiles");
@@ -1609,7 +1648,8 @@ mist_status mist_debug_eval_tiles(mist_space* S, const int32_t* tiles, int32_t n
     ea.dump = (double*)dout.p;
     ea.dump_off = (const int64_t*)doff.p;
     int k = launch_pairs(ea, st);  // pair constants, and the tile counters' reset
-    if (!k) k = launch_eval(ea, mode_grid(S, kModeDump), kModeDump, st);
+    if (!k) k = S->bounded ? launch_search(ea, mode_grid(S, kModeDump, S->tiles.size()), kModeDump, st)
+                           : launch_eval(ea, mode_grid(S, kModeDump, S->tiles.size()), kModeDump, st);
     if (k) return drained(fail_hip((hipError_t)k, "debug tiles: launch"));
     e = copy_async(out, dout.p, (size_t)total * kDumpWords * sizeof(double), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
