@@ -448,5 +448,74 @@ __device__ __forceinline__ void lds_store(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+// ---------------------------------------------------------------------------------------
+// Per-id evaluation with the same level functions (parity, listed configurations and result
+// extraction).
+// ---------------------------------------------------------------------------------------
+struct OneVal {
+  double t, d, mem, obj;
+};
+
+// The digits of a configuration id: binary search of the group, mixed-radix decode.
+struct Digits {
+  int64_t group;
+  int p, c, z, iw, ig, io, ia;
+};
+
+__device__ __forceinline__ Digits decode_one(const EvalArgs& a, uint64_t id) {
+  int64_t lo = 0, hi = a.n_groups;
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) / 2;
+    if (a.groups[mid].base <= id) lo = mid;
+    else hi = mid;
+  }
+  const DevGroup& g = a.groups[lo];
+  const uint64_t R = (uint64_t)a.R;
+  uint64_t v = id - g.base;
+  Digits x;
+  x.group = lo;
+  x.ia = (int)(v % R);
+  v /= R;
+  x.io = (int)(v % R);
+  v /= R;
+  x.ig = (int)(v % R);
+  v /= R;
+  x.iw = (int)(v % R);
+  v /= R;
+  x.z = (int)(v % 4);
+  v /= 4;
+  x.c = (int)(v % (uint64_t)(g.l + 1));
+  x.p = (int)(v / (uint64_t)(g.l + 1));
+  return x;
+}
+
+__device__ OneVal eval_one(const EvalArgs& a, const Digits& x) {
+  const DevGroup g = a.groups[x.group];
+  const DevHw& hw = a.hws[g.hw];
+  const double* r = a.ratio;
+  const double* om = a.ratio + a.R;
+  const int64_t ke = g.k < g.G ? g.k : g.G;
+  const double* tab = &hw.itab[0][0];
+  const PairK P = pair_level(a.m, g.PP, g.k, g.l, a.pairs[g.pair_begin + x.p], hw);
+  const CkptK K = ckpt_level(P, g.l, x.c, ke);
+  const ZeroK Z = zero_level(P, x.z);
+  const WoGoK W = wogo_levels(P, Z, r[x.iw], om[x.iw], r[x.ig], om[x.ig]);
+  const OoK O = oo_level(oo_inputs(P, K, Z, W), r[x.io], om[x.io], hw.iP);
+  const double ra = r[x.ia];
+  const double SO = __builtin_fma(ra, P.A2, om[x.ia] * K.KA);
+  const double H2Ds = __builtin_fma(ra, K.A, W.HW) * hw.iP;
+  const double D2Hs = __builtin_fma(ra, K.A, W.DG) * hw.iP;
+  OneVal res;
+  res.mem = O.Bmax + SO;
+  res.t = interference<kTabStride>(K.C, Z.G2Gs, H2Ds, D2Hs, tab);
+  const double T1 = interference<kTabStride>(K.C, Z.G2Gf, H2Ds + O.H2Dx, D2Hs + O.D2Hx, tab);
+  res.d = T1 - res.t;
+  res.obj = __builtin_fma((double)g.G, res.t, res.d);
+  return res;
+}
+
+// One configuration by id.
+__device__ __forceinline__ OneVal eval_one(const EvalArgs& a, uint64_t id) { return eval_one(a, decode_one(a, id)); }
+
 }  // namespace
 }  // namespace mist

@@ -141,6 +141,8 @@ struct mist_space {
   uint64_t* d_part_aid = nullptr;
   double* d_alpha_obj = nullptr;
   uint64_t* d_alpha_id = nullptr;
+  void* d_ws = nullptr;  // workspace of the extraction calls
+  size_t ws_bytes = 0;
   int32_t cus = 0;
   int32_t device = 0;  // the HIP device the space was created on
   // exact frontier (mist_eval_pareto_exact)
@@ -174,6 +176,7 @@ struct mist_space {
   int64_t* d_seg = nullptr;
   int64_t* d_seg_end = nullptr;  // end of each group's candidates after the pre-filter
   int64_t* d_front_cnt = nullptr;
+  std::vector<int64_t> front_cnt;  // host copy of the last call's counts (empty: not fetched)
   // Pinned host staging of the per-tile counts and the offset tables (copies to and from it
   // run without a staging step); allocated by the first exact frontier, freed by destroy.
   void* h_pinned = nullptr;
@@ -558,8 +561,13 @@ mist::EvalArgs eval_args(const mist_space* S) {
   return a;
 }
 
+mist_status have_results(const mist_space* S) {
+  return S->evaluated ? MIST_OK : fail(MIST_E_STATE, "mist_eval_space has not been called");
+}
+
 mist_status wait_results(mist_space* S) {
-  if (!S->evaluated) return fail(MIST_E_STATE, "mist_eval_space has not been called");
+  const mist_status rc = have_results(S);
+  if (rc) return rc;
   const hipError_t e = hipStreamSynchronize(S->stream);
   if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
   return MIST_OK;
@@ -591,11 +599,12 @@ void decode_host(const mist_space* S, uint64_t id, mist_config* c) {
   c->ao = S->ratio_om[c->ao_idx];
 }
 
-// Device evaluation of ids for result extraction: out[4*i..] = t, d, mem, obj.
+// Device evaluation of listed configurations: out[4*i..] = t, d, mem, obj.
 mist_status eval_ids_impl(mist_space* S, const uint64_t* ids, int64_t n, double* out, hipStream_t st) {
   if (n == 0) return MIST_OK;
-  for (int64_t i = 0; i < n; ++i)
-    if (ids[i] >= S->n_configs) return fail(MIST_E_RANGE, "id out of range");
+  bool bad = false;
+  for (int64_t i = 0; i < n; ++i) bad |= ids[i] >= S->n_configs;
+  if (bad) return fail(MIST_E_RANGE, "id out of range");
   TempBuf dids(S, (size_t)n * sizeof(uint64_t), st);
   TempBuf dout(S, (size_t)n * 4 * sizeof(double), st);
   if (!dids.p || !dout.p) return fail(MIST_E_NOMEM, "device allocation failed: eval_ids");
@@ -616,39 +625,39 @@ mist_status eval_ids_impl(mist_space* S, const uint64_t* ids, int64_t n, double*
   return MIST_OK;
 }
 
-int32_t bucket_host(const mist_space* S, const DevHw& h, double mem) {
-  for (int32_t j = 0; j < S->NB; ++j)
-    if (mem <= h.edge[j]) return j;
-  return -1;
+// The space's device workspace of at least `bytes`, kept for later calls.  Every call that uses it
+// waits for its own work before it returns.
+void* workspace(mist_space* S, size_t bytes, hipStream_t st) {
+  if (bytes > S->ws_bytes) {
+    dev_free_one(S, S->d_ws);
+    S->ws_bytes = 0;
+    S->d_ws = dev_alloc(S, bytes, st);
+    if (S->d_ws) S->ws_bytes = bytes;
+  }
+  return S->d_ws;
 }
 
-mist_status fill_results(mist_space* S, const uint64_t* ids, const double* objs, int64_t n, mist_result* out) {
-  std::vector<uint64_t> want;
-  for (int64_t i = 0; i < n; ++i)
-    if (ids[i] != MIST_NONE) want.push_back(ids[i]);
-  std::vector<double> vals(want.size() * 4);
-  mist_status rc = eval_ids_impl(S, want.data(), (int64_t)want.size(), vals.data(), S->stream);
+// Copies back what the stream's work leaves at src and waits.
+mist_status fetch(void* dst, const void* src, size_t bytes, hipStream_t st, const char* what) {
+  hipError_t e = copy_async(dst, src, bytes, hipMemcpyDeviceToHost, st);
+  const hipError_t w = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = w;
+  return e == hipSuccess ? MIST_OK : fail_hip(e, what);
+}
+
+// Results of n configurations whose ids and objectives (with n_alpha > 0: weighted values) lie on the
+// device, formed there behind the work queued on st.
+mist_status fetch_results(mist_space* S, const uint64_t* ids, const double* objs, const uint64_t* key, int32_t n_alpha,
+                          int64_t n, mist_result* out, hipStream_t st) {
+  if (n == 0) return MIST_OK;
+  mist_result* w = (mist_result*)workspace(S, (size_t)n * sizeof(mist_result), st);
+  if (!w) return fail(MIST_E_NOMEM, "device allocation failed: results");
+  const int k = launch_results(eval_args(S), ids, objs, key, n_alpha, n, w, st);
+  if (k) return fail_hip((hipError_t)k, "results launch");
+  const mist_status rc = fetch(out, w, (size_t)n * sizeof(mist_result), st, "results");
   if (rc) return rc;
-  size_t w = 0;
-  for (int64_t i = 0; i < n; ++i) {
-    mist_result& r = out[i];
-    std::memset(&r, 0, sizeof(r));
-    r.id = ids[i];
-    r.obj = objs[i];
-    if (ids[i] == MIST_NONE) {
-      r.t = r.d = r.mem = std::numeric_limits<double>::infinity();
-      r.bucket = -1;
-      r.cfg.hw = -1;
-      continue;
-    }
-    r.t = vals[4 * w + 0];
-    r.d = vals[4 * w + 1];
-    r.mem = vals[4 * w + 2];
-    if (vals[4 * w + 3] != objs[i]) return fail(MIST_E_DEVICE, "re-evaluated objective differs");
-    ++w;
-    decode_host(S, r.id, &r.cfg);
-    r.bucket = bucket_host(S, S->hws[r.cfg.hw], r.mem);
-  }
+  for (int64_t i = 0; i < n; ++i)
+    if (out[i].pad) return fail(MIST_E_DEVICE, "re-evaluated configuration differs");
   return MIST_OK;
 }
 
@@ -1033,6 +1042,7 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
       if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
     }
     S->exact_done = false;
+    S->front_cnt.clear();
     if (!S->d_filt) {
       // Windows: ceil(configurations / div) slots per tile.
       const int64_t R2 = (int64_t)S->R * S->R;
@@ -1295,30 +1305,18 @@ mist_status mist_get_pareto_exact(mist_space* S, int64_t g, mist_result* out, in
   if (!S || !n_out || (!out && cap > 0)) return fail(MIST_E_INVALID, "null argument");
   if (!S->exact_done) return fail(MIST_E_STATE, "mist_eval_pareto_exact has not been called");
   if (g < 0 || g >= (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group out of range");
-  hipError_t e = hipStreamSynchronize(S->exact_stream);
-  if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
   try {
-    int64_t n = 0;
-    e = copy_sync(&n, S->d_front_cnt + g, sizeof(int64_t), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpy frontier count");
+    if (S->front_cnt.empty()) {  // every group's count comes back with the first
+      std::vector<int64_t> cnt(S->groups.size());
+      const mist_status rc = fetch(cnt.data(), S->d_front_cnt, cnt.size() * sizeof(int64_t), S->exact_stream, "frontier counts");
+      if (rc) return rc;
+      S->front_cnt.swap(cnt);
+    }
+    const int64_t n = S->front_cnt[(size_t)g];
     *n_out = n;
     if (n > cap) return fail(MIST_E_RANGE, "cap is smaller than the frontier");
-    if (n == 0) return MIST_OK;
     const size_t b = (size_t)S->h_seg[g];
-    std::vector<uint64_t> keys(n), ids(n);
-    std::vector<double> objs(n);
-    e = copy_sync(keys.data(), S->d_front_key + b, n * 8, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = copy_sync(ids.data(), S->d_front_id + b, n * 8, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = copy_sync(objs.data(), S->d_front_obj + b, n * 8, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpy frontier");
-    mist_status rc = fill_results(S, ids.data(), objs.data(), n, out);
-    if (rc) return rc;
-    for (int64_t i = 0; i < n; ++i) {
-      double mem;
-      std::memcpy(&mem, &keys[i], 8);
-      if (mem != out[i].mem) return fail(MIST_E_DEVICE, "re-evaluated memory differs");
-    }
-    return MIST_OK;
+    return fetch_results(S, S->d_front_id + b, S->d_front_obj + b, S->d_front_key + b, 0, n, out, S->exact_stream);
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1327,17 +1325,10 @@ mist_status mist_get_pareto_exact(mist_space* S, int64_t g, mist_result* out, in
 mist_status mist_get_best(mist_space* S, int64_t g0, int64_t n, mist_result* out) {
   if (!S || (!out && n > 0)) return fail(MIST_E_INVALID, "null argument");
   if (g0 < 0 || n < 0 || g0 + n > (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group range");
-  mist_status rc = wait_results(S);
-  if (rc) return rc;
-  if (n == 0) return MIST_OK;
+  const mist_status rc = n == 0 ? wait_results(S) : have_results(S);
+  if (rc || n == 0) return rc;
   try {
-    std::vector<uint64_t> ids(n);
-    std::vector<double> objs(n);
-    hipError_t e = copy_sync(ids.data(), S->d_best_id + g0, n * sizeof(uint64_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess)
-      e = copy_sync(objs.data(), S->d_best_obj + g0, n * sizeof(double), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpy best");
-    return fill_results(S, ids.data(), objs.data(), n, out);
+    return fetch_results(S, S->d_best_id + g0, S->d_best_obj + g0, nullptr, 0, n, out, S->stream);
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1347,47 +1338,11 @@ mist_status mist_get_alpha(mist_space* S, int64_t g0, int64_t n, mist_result* ou
   if (!S || (!out && n > 0)) return fail(MIST_E_INVALID, "null argument");
   if (S->A == 0) return fail(MIST_E_STATE, "the space has no weight samples");
   if (g0 < 0 || n < 0 || g0 + n > (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group range");
-  mist_status rc = wait_results(S);
-  if (rc) return rc;
-  if (n == 0) return MIST_OK;
+  const mist_status rc = n == 0 ? wait_results(S) : have_results(S);
+  if (rc || n == 0) return rc;
   try {
-    const size_t A = (size_t)S->A, m = (size_t)n * A;
-    std::vector<uint64_t> ids(m);
-    std::vector<double> objs(m);
-    hipError_t e = copy_sync(ids.data(), S->d_alpha_id + (size_t)g0 * A, m * sizeof(uint64_t),
-                             hipMemcpyDeviceToHost);
-    if (e == hipSuccess)
-      e = copy_sync(objs.data(), S->d_alpha_obj + (size_t)g0 * A, m * sizeof(double), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpy weight-sample results");
-    std::vector<uint64_t> want;
-    for (size_t i = 0; i < m; ++i)
-      if (ids[i] != MIST_NONE) want.push_back(ids[i]);
-    std::vector<double> vals(want.size() * 4);
-    rc = eval_ids_impl(S, want.data(), (int64_t)want.size(), vals.data(), S->stream);
-    if (rc) return rc;
-    size_t w = 0;
-    for (size_t i = 0; i < m; ++i) {
-      mist_result& r = out[i];
-      std::memset(&r, 0, sizeof(r));
-      r.id = ids[i];
-      r.obj = objs[i];
-      if (ids[i] == MIST_NONE) {
-        r.t = r.d = r.mem = std::numeric_limits<double>::infinity();
-        r.bucket = -1;
-        r.cfg.hw = -1;
-        continue;
-      }
-      r.t = vals[4 * w + 0];
-      r.d = vals[4 * w + 1];
-      r.mem = vals[4 * w + 2];
-      ++w;
-      decode_host(S, r.id, &r.cfg);
-      const size_t a = i % A;
-      const double v = std::fma(S->alphas[a] * (double)r.cfg.G, r.t, S->betas[a] * r.d);
-      if (v != r.obj) return fail(MIST_E_DEVICE, "re-evaluated weighted objective differs");
-      r.bucket = bucket_host(S, S->hws[r.cfg.hw], r.mem);
-    }
-    return MIST_OK;
+    const size_t at = (size_t)g0 * (size_t)S->A;
+    return fetch_results(S, S->d_alpha_id + at, S->d_alpha_obj + at, nullptr, S->A, n * S->A, out, S->stream);
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1397,39 +1352,40 @@ mist_status mist_plan_pipeline(mist_space* S, int32_t hw, int32_t pp, mist_plan*
   if (!S || !out) return fail(MIST_E_INVALID, "null argument");
   if (hw < 0 || hw >= (int32_t)S->hw.size()) return fail(MIST_E_RANGE, "hardware sample out of range");
   if (pp < 0 || pp > MIST_MAX_STAGES) return fail(MIST_E_INVALID, "pp out of range");
-  mist_status rc = wait_results(S);
+  mist_status rc = have_results(S);
   if (rc) return rc;
   try {
-    const size_t A = (size_t)S->A, ng = S->groups.size();
-    std::vector<uint64_t> best(ng), alpha(ng * A);
-    hipError_t e = copy_sync(best.data(), S->d_best_id, ng * sizeof(uint64_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess && A)
-      e = copy_sync(alpha.data(), S->d_alpha_id, ng * A * sizeof(uint64_t), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpy frontier points");
-    std::vector<mist_stage_point> pts;
-    std::vector<uint64_t> ids;
-    for (size_t g = 0; g < ng; ++g) {
-      if (S->groups[g].hw != hw || (pp != 0 && S->groups[g].PP != pp)) continue;
-      std::vector<uint64_t> mine(1 + A);
-      mine[0] = best[g];
-      for (size_t a = 0; a < A; ++a) mine[1 + a] = alpha[g * A + a];
-      std::sort(mine.begin(), mine.end());
-      mine.erase(std::unique(mine.begin(), mine.end()), mine.end());
-      const DevGroup& G = S->groups[g];
-      for (uint64_t id : mine) {
-        if (id == MIST_NONE) continue;
-        mist_stage_point p{};
-        p.G = G.G; p.PP = G.PP; p.k = G.k; p.l = G.l; p.id = id;
-        pts.push_back(p);
-        ids.push_back(id);
-      }
+    // The hardware sample's groups are consecutive; their points come back in one copy.
+    size_t g0 = 0, g1 = S->groups.size();
+    while (g0 < g1 && S->groups[g0].hw != hw) ++g0;
+    while (g1 > g0 && S->groups[g1 - 1].hw != hw) --g1;
+    const size_t per = 1 + (size_t)S->A, n = (g1 - g0) * per;
+    std::vector<PlanPoint> got(n);
+    if (n) {
+      PlanPoint* w = (PlanPoint*)workspace(S, n * sizeof(PlanPoint), S->stream);
+      if (!w) return fail(MIST_E_NOMEM, "device allocation failed: frontier points");
+      const int k = launch_points(eval_args(S), S->d_best_id, S->d_alpha_id, S->A, (int64_t)g0, (int64_t)(g1 - g0), w,
+                                  S->stream);
+      if (k) return fail_hip((hipError_t)k, "frontier points launch");
+      rc = fetch(got.data(), w, n * sizeof(PlanPoint), S->stream, "frontier points");
+    } else {
+      rc = wait_results(S);
     }
-    std::vector<double> vals(ids.size() * 4);
-    rc = eval_ids_impl(S, ids.data(), (int64_t)ids.size(), vals.data(), S->stream);
     if (rc) return rc;
-    for (size_t i = 0; i < pts.size(); ++i) {
-      pts[i].t = vals[4 * i + 0];
-      pts[i].d = vals[4 * i + 1];
+    std::vector<mist_stage_point> pts;
+    pts.reserve(n);
+    for (size_t g = g0; g < g1; ++g) {
+      const DevGroup& G = S->groups[g];
+      if (pp != 0 && G.PP != pp) continue;
+      PlanPoint* mine = got.data() + (g - g0) * per;
+      std::sort(mine, mine + per, [](const PlanPoint& x, const PlanPoint& y) { return x.id < y.id; });
+      for (size_t i = 0; i < per; ++i) {
+        if (mine[i].id == MIST_NONE || (i && mine[i].id == mine[i - 1].id)) continue;
+        mist_stage_point p{};
+        p.G = G.G; p.PP = G.PP; p.k = G.k; p.l = G.l;
+        p.id = mine[i].id; p.t = mine[i].t; p.d = mine[i].d;
+        pts.push_back(p);
+      }
     }
     rc = mist_plan_points(pts.data(), (int64_t)pts.size(), S->model.n_layers, pp, out);
     if (rc) return rc;
@@ -1444,27 +1400,28 @@ mist_status mist_get_buckets(mist_space* S, int64_t g0, int64_t n, uint64_t* ids
                              uint64_t* masks) {
   if (!S) return fail(MIST_E_INVALID, "space is null");
   if (g0 < 0 || n < 0 || g0 + n > (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group range");
-  mist_status rc = wait_results(S);
-  if (rc) return rc;
-  if (n == 0) return MIST_OK;
+  mist_status rc = n == 0 || (!ids && !objs && !masks) ? wait_results(S) : have_results(S);
+  if (rc || n == 0) return rc;
   try {
+    // The device tables hold 64 buckets per group: fewer are packed there first.
     const int NB = S->NB;
-    std::vector<uint64_t> bid((size_t)n * 64);
-    std::vector<double> bobj((size_t)n * 64);
-    hipError_t e = copy_sync(bid.data(), S->d_bucket_id + g0 * 64, bid.size() * sizeof(uint64_t),
-                             hipMemcpyDeviceToHost);
-    if (e == hipSuccess)
-      e = copy_sync(bobj.data(), S->d_bucket_obj + g0 * 64, bobj.size() * sizeof(double),
-                    hipMemcpyDeviceToHost);
-    if (e == hipSuccess && masks)
-      e = copy_sync(masks, S->d_frontier + g0, n * sizeof(uint64_t), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpy buckets");
-    for (int64_t i = 0; i < n; ++i)
-      for (int j = 0; j < NB; ++j) {
-        if (ids) ids[i * NB + j] = bid[i * 64 + j];
-        if (objs) objs[i * NB + j] = bobj[i * 64 + j];
+    const size_t words = (size_t)n * (size_t)NB;
+    hipStream_t st = S->stream;
+    const uint64_t* src[2] = {S->d_bucket_id + g0 * 64, (const uint64_t*)S->d_bucket_obj + g0 * 64};
+    void* dst[2] = {ids, objs};
+    if (NB < 64 && (ids || objs)) {
+      uint64_t* w = (uint64_t*)workspace(S, 2 * words * sizeof(uint64_t), st);
+      if (!w) return fail(MIST_E_NOMEM, "device allocation failed: buckets");
+      for (int i = 0; i < 2; ++i) {
+        const int k = dst[i] ? launch_rows(src[i], NB, n, w + i * words, st) : 0;
+        if (k) return fail_hip((hipError_t)k, "buckets launch");
+        src[i] = w + i * words;
       }
-    return MIST_OK;
+    }
+    for (int i = 0; i < 2 && !rc; ++i)
+      if (dst[i]) rc = fetch(dst[i], src[i], words * sizeof(uint64_t), st, "buckets");
+    if (!rc && masks) rc = fetch(masks, S->d_frontier + g0, (size_t)n * sizeof(uint64_t), st, "frontier masks");
+    return rc;
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1473,24 +1430,22 @@ mist_status mist_get_buckets(mist_space* S, int64_t g0, int64_t n, uint64_t* ids
 mist_status mist_get_pareto(mist_space* S, int64_t g, mist_result* out, int32_t cap, int32_t* n_out) {
   if (!S || !n_out) return fail(MIST_E_INVALID, "null argument");
   if (g < 0 || g >= (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group index");
-  const int NB = S->NB;
-  std::vector<uint64_t> ids(NB);
-  std::vector<double> objs(NB);
-  uint64_t mask = 0;
-  mist_status rc = mist_get_buckets(S, g, 1, ids.data(), objs.data(), &mask);
+  mist_status rc = have_results(S);
   if (rc) return rc;
-  std::vector<uint64_t> fid;
-  std::vector<double> fobj;
-  for (int j = 0; j < NB; ++j)
-    if (mask >> j & 1) {
-      fid.push_back(ids[j]);
-      fobj.push_back(objs[j]);
-    }
-  *n_out = (int32_t)fid.size();
-  if ((int32_t)fid.size() > cap) return fail(MIST_E_RANGE, "output capacity too small");
-  if (fid.empty()) return MIST_OK;
+  uint64_t mask = 0;
+  rc = fetch(&mask, S->d_frontier + g, sizeof(mask), S->stream, "frontier mask");
+  if (rc) return rc;
+  *n_out = (int32_t)__builtin_popcountll(mask);
+  if (*n_out > cap) return fail(MIST_E_RANGE, "output capacity too small");
+  if (*n_out == 0) return MIST_OK;
   if (!out) return fail(MIST_E_INVALID, "out is null");
-  return fill_results(S, fid.data(), fobj.data(), (int64_t)fid.size(), out);
+  mist_result row[MIST_MAX_BUCKETS];  // every bucket's winner, of which the staircase is kept
+  rc = fetch_results(S, S->d_bucket_id + g * 64, S->d_bucket_obj + g * 64, nullptr, 0, S->NB, row, S->stream);
+  if (rc) return rc;
+  int32_t w = 0;
+  for (int j = 0; j < S->NB; ++j)
+    if (mask >> j & 1) out[w++] = row[j];
+  return MIST_OK;
 }
 
 mist_status mist_space_info(const mist_space* S, uint64_t* n_configs, int64_t* n_groups, int32_t* n_buckets) {

@@ -201,6 +201,17 @@ int launch_reduce(const ReduceArgs& a, void* stream);
 int launch_eval_ids(const EvalArgs& a, const uint64_t* ids, int64_t n, double* out, void* stream);
 int launch_filter(const EvalArgs& a, const double* bucket_obj, const uint64_t* bucket_id, FiltEntry* filt,
                   void* stream);
+// Result extraction, mist_extract.hip: results in the caller's layout; pad is 1 where the values formed
+// there differ from objs (or from the memory bits in key, unless nullptr).
+struct PlanPoint {
+  uint64_t id;
+  double t, d;
+};
+int launch_results(const EvalArgs& a, const uint64_t* ids, const double* objs, const uint64_t* key, int32_t n_alpha,
+                   int64_t n, mist_result* out, void* stream);
+int launch_points(const EvalArgs& a, const uint64_t* best, const uint64_t* alpha, int32_t n_alpha, int64_t g0, int64_t n,
+                  PlanPoint* out, void* stream);
+int launch_rows(const uint64_t* in, int32_t NB, int64_t n, uint64_t* out, void* stream);
 // Exact frontier, mist_exact.hip: the candidates of group g are [seg[g], seg[g+1]).  The
 // pre-filter drops, per group, candidates that one of strictly smaller memory dominates and
 // moves the rest to the front (their end in seg_end); one segmented sort by memory over

@@ -535,60 +535,7 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a) {
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// Per-id evaluation with the same level functions (parity and result extraction).
-// ---------------------------------------------------------------------------------------
-struct OneVal {
-  double t, d, mem, obj;
-};
-
-// One configuration by id: binary search of the group, mixed-radix decode, and the level
-// functions of the evaluation kernel.
-__device__ OneVal eval_one(const EvalArgs& a, uint64_t id) {
-  int64_t lo = 0, hi = a.n_groups;
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) / 2;
-    if (a.groups[mid].base <= id) lo = mid;
-    else hi = mid;
-  }
-  const DevGroup g = a.groups[lo];
-  const DevHw& hw = a.hws[g.hw];
-  const uint64_t R = (uint64_t)a.R;
-  uint64_t v = id - g.base;
-  const int ia = (int)(v % R);
-  v /= R;
-  const int io = (int)(v % R);
-  v /= R;
-  const int ig = (int)(v % R);
-  v /= R;
-  const int iw = (int)(v % R);
-  v /= R;
-  const int z = (int)(v % 4);
-  v /= 4;
-  const int c = (int)(v % (uint64_t)(g.l + 1));
-  const int p = (int)(v / (uint64_t)(g.l + 1));
-  const double* r = a.ratio;
-  const double* om = a.ratio + a.R;
-  const int64_t ke = g.k < g.G ? g.k : g.G;
-  const double* tab = &hw.itab[0][0];
-  const PairK P = pair_level(a.m, g.PP, g.k, g.l, a.pairs[g.pair_begin + p], hw);
-  const CkptK K = ckpt_level(P, g.l, c, ke);
-  const ZeroK Z = zero_level(P, z);
-  const WoGoK W = wogo_levels(P, Z, r[iw], om[iw], r[ig], om[ig]);
-  const OoK O = oo_level(oo_inputs(P, K, Z, W), r[io], om[io], hw.iP);
-  const double ra = r[ia];
-  const double SO = __builtin_fma(ra, P.A2, om[ia] * K.KA);
-  const double H2Ds = __builtin_fma(ra, K.A, W.HW) * hw.iP;
-  const double D2Hs = __builtin_fma(ra, K.A, W.DG) * hw.iP;
-  OneVal res;
-  res.mem = O.Bmax + SO;
-  res.t = interference<kTabStride>(K.C, Z.G2Gs, H2Ds, D2Hs, tab);
-  const double T1 = interference<kTabStride>(K.C, Z.G2Gf, H2Ds + O.H2Dx, D2Hs + O.D2Hx, tab);
-  res.d = T1 - res.t;
-  res.obj = __builtin_fma((double)g.G, res.t, res.d);
-  return res;
-}
-
+// Per-id evaluation (parity and listed configurations).
 __global__ __launch_bounds__(256) void k_eval_ids(EvalArgs a, const uint64_t* __restrict__ ids,
                                                   int64_t n, double* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

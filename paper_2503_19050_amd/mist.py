@@ -325,7 +325,7 @@ class Space:
         return np.ctypeslib.as_array(self._best_raw(g0, n))[:n]
 
     def _best_raw(self, g0: int, n: int):
-        out = (Result * max(n, 1))()
+        out = (Result * max(n, 1)).from_buffer(np.empty(max(n, 1) * ctypes.sizeof(Result), dtype=np.uint8))
         _check(self.L, self.L.mist_get_best(self.h, g0, n, out))
         return out
 
