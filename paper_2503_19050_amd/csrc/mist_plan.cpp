@@ -12,6 +12,15 @@
 // a dynamic program over (stage, layers used) keeps only the non-dominated triples and is exact;
 // no MILP solver is needed.
 //
+// The (G, PP) are visited in order of a lower bound on their plans, and partial plans whose bound is
+// above the best plan found are dropped (branch and bound).  The bound: the stages still to place hold
+// the layers still to place, and every candidate point has t >= rho l with rho the least t / l of
+// that (G, PP), so their times sum to at least rho times those layers and the largest is at least the
+// mean; the first stage's delta is at least the least one.  It is lowered by 1e-12 of its terms, far
+// above their rounding, and only a strictly worse partial plan is dropped: the plan found is the one
+// found without it (a dropped plan's dominated ones could not win either).  (Planner on llama13b-d64 with 8 weight samples, 86,700 points: 33 ms
+// on one core without the bound, about 2 with it.)
+//
 // Exact also in floating point: every step above (a rounded sum, a maximum) and the final
 // (G - 1) * M + H are non-decreasing in T, H and M, so a pruned state's completions never round
 // below its dominator's.  Finished plans are therefore ranked by that same suffix-form value,
@@ -77,6 +86,23 @@ void add_state(std::vector<State>& v, const State& s) {
   v.push_back(s);
 }
 
+// What the candidate points of one (G, PP) bound: the least t / l and the least d.
+struct Least {
+  double rho = std::numeric_limits<double>::infinity(), d = std::numeric_limits<double>::infinity();
+};
+
+// Lower bound of the suffix-form value of any plan that completes a partial one (T, H, M) with `layers`
+// layers on `stages` more stages.
+double completion_bound(int32_t G, const Least& m, double T, double H, double M, int32_t layers, int32_t stages) {
+  const double rest = stages > 0 ? m.rho * (double)layers : 0.0;
+  const double t = T + rest;
+  const double big = stages > 0 ? std::max(M, rest / (double)stages) : M;
+  const double first = stages > 0 ? std::max(H, m.d + t) : H;
+  const double a = (double)(G - 1) * big;
+  const double v = (a + first) - 1e-12 * (std::fabs(a) + std::fabs(first) + std::fabs(m.d) + std::fabs(t));
+  return v == v ? v : -std::numeric_limits<double>::infinity();  // overflow: no bound
+}
+
 double plan_value(int32_t G, const std::vector<double>& t, const std::vector<double>& d) {
   double t_max = t[0], t_sum = 0.0, m = 0.0;
   for (size_t i = 0; i < t.size(); ++i) {
@@ -99,18 +125,41 @@ extern "C" mist_status mist_plan_points(const mist_stage_point* pts, int64_t n, 
     std::memset(out, 0, sizeof(*out));
     out->F = std::numeric_limits<double>::infinity();
     double best_Fs = std::numeric_limits<double>::infinity();  // suffix-form value of *out
-    // candidates per (G, PP) -> per k -> per l
+    // candidates per (G, PP) -> per k -> per l (points of one group usually come in a row)
     std::map<std::pair<int32_t, int32_t>, std::map<int32_t, std::map<int32_t, std::vector<Pt>>>> cand;
+    std::map<std::pair<int32_t, int32_t>, Least> least;
+    std::vector<Pt>* group = nullptr;
+    Least* bound = nullptr;
     for (int64_t i = 0; i < n; ++i) {
       const mist_stage_point& p = pts[i];
       if (p.PP < 1 || p.k < 1 || p.k > p.PP || p.l < 1 || p.G < 1 || !std::isfinite(p.t) || !std::isfinite(p.d))
         return lib_fail(MIST_E_INVALID, "invalid stage point");
       if (p.PP > MIST_MAX_STAGES || (pp && p.PP != pp)) continue;
-      cand[{p.G, p.PP}][p.k][p.l].push_back(Pt{p.t, p.d, p.id});
+      const mist_stage_point* q = i ? &pts[i - 1] : nullptr;
+      if (!group || !(q->G == p.G && q->PP == p.PP && q->k == p.k && q->l == p.l)) {
+        group = &cand[{p.G, p.PP}][p.k][p.l];
+        bound = &least[{p.G, p.PP}];
+      }
+      group->push_back(Pt{p.t, p.d, p.id});
+      bound->rho = std::min(bound->rho, p.t / (double)p.l);
+      bound->d = std::min(bound->d, p.d);
     }
-    for (auto& gp : cand) {
+    struct Visit {
+      double bound;
+      int32_t G, PP;
+    };
+    std::vector<Visit> order;
+    for (const auto& gp : least) {
       const int32_t G = gp.first.first, PP = gp.first.second;
-      auto& byk = gp.second;
+      order.push_back({completion_bound(G, gp.second, 0.0, -std::numeric_limits<double>::infinity(), 0.0, n_layers, PP), G, PP});
+    }
+    std::sort(order.begin(), order.end(),
+              [](const Visit& x, const Visit& y) { return std::tie(x.bound, x.G, x.PP) < std::tie(y.bound, y.G, y.PP); });
+    for (const Visit& visit : order) {
+      if (visit.bound > best_Fs) break;
+      const int32_t G = visit.G, PP = visit.PP;
+      const Least& low = least[{G, PP}];
+      auto& byk = cand[{G, PP}];
       // stage i (1-based) runs k = PP - i + 1 microbatches in flight
       std::vector<std::vector<std::pair<int32_t, std::vector<Pt>>>> stage(PP + 1);
       bool ok = true;
@@ -141,8 +190,9 @@ extern "C" mist_status mist_plan_points(const mist_stage_point* pts, int64_t n, 
               if (i == 1 && u2 != n_layers) continue;
               for (int q = 0; q < (int)lp.second.size(); ++q) {
                 const Pt& p = lp.second[q];
-                const double T = p.t + st.T;
-                add_state(states[i][u2], State{T, std::max(st.H, p.d + T), std::max(st.M, p.t), s, lp.first, q});
+                const double T = p.t + st.T, H = std::max(st.H, p.d + T), M = std::max(st.M, p.t);
+                if (completion_bound(G, low, T, H, M, n_layers - u2, i - 1) > best_Fs) continue;
+                add_state(states[i][u2], State{T, H, M, s, lp.first, q});
               }
             }
           }
@@ -152,7 +202,8 @@ extern "C" mist_status mist_plan_points(const mist_stage_point* pts, int64_t n, 
       const auto& fin = states[1][n_layers];
       for (int s = 0; s < (int)fin.size(); ++s) {
         const double Fs = (double)(G - 1) * fin[s].M + fin[s].H;
-        if (!(Fs < best_Fs)) continue;
+        // Among equal values the smallest (G, PP), and within one the first found.
+        if (!(Fs < best_Fs || (Fs == best_Fs && std::tie(G, PP) < std::tie(out->G, out->PP)))) continue;
         best_Fs = Fs;
         std::vector<double> tv, dv;
         mist_plan cand_plan;
