@@ -57,18 +57,19 @@ __device__ __forceinline__ void pool_holes(const EvalArgs& a, unsigned long long
 // exact frontier's variant the threshold is pm, the least objective of the lower buckets, which
 // does not increase with the bucket: the lowest bucket of the range decides.
 // ---------------------------------------------------------------------------------------
-// What a strip needs of its unit (pair, recomputed layers, ZeRO level).
+// What a strip needs of its unit (pair, recomputed layers, ZeRO level).  Kept small: the wave's records,
+// its queue and its tables decide how many blocks a CU holds.
 struct UnitRec {
-  double Sw, Sg, sw, sg;     // resident-if-kept weights and gradients, their shard factors
-  double Wb2, Obg, So, Obo;  // double-buffered fp16 unit, optimizer-step unit parts, optimizer states
-  double Rc, Xd;             // recompute unit, logits
+  double Pw, iD, Wb2;        // stage fp16 parameter bytes, 1 / DP, double-buffered fp16 unit
+  double So, Obo;            // optimizer states, their part of the optimizer-step unit
+  double Xd;                 // logits
   double A, KA, A2;          // microbatch activations, in-flight stash, offload buffers
   double C, gs, gf;          // compute, GPU-GPU stable and first microbatch
-  int32_t unit, pad;
+  int32_t unit, ckpt;        // unit index (its last two bits: the ZeRO level); whether layers are recomputed
 };
-static_assert(sizeof(UnitRec) == 136, "17 doubles: consecutive records start in different banks");
 
-constexpr int kUnits = 32;       // live unit records per wave
+constexpr int kQueue = 128;  // queue of columns: fewer than 64 left over, and one push of 64
+
 constexpr int kRangeLevels = 7;  // range maxima over 1, 2, 4, .. 64 buckets
 
 // Largest of the thresholds of buckets a..b (0 <= a <= b <= 63): level e of tab holds the maxima over
@@ -79,6 +80,10 @@ __device__ __forceinline__ double range_max(const float* __restrict__ tab, unsig
   return (double)__builtin_fmaxf(row[a], row[b + 1u - (1u << e)]);
 }
 
+// Live unit records per wave: as many as four blocks per CU leave room for.
+template <int MODE>
+constexpr int unit_slots() { return MODE == kModeAlpha || MODE == kModeSeedAlpha ? 28 : 32; }
+
 template <int R, int MODE>
 __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* __restrict__ ratio,
                                                       const PairK* __restrict__ pk) {
@@ -87,12 +92,16 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
   constexpr bool SD = MODE == kModeSeed || MODE == kModeSeedAlpha;
   constexpr bool AL = MODE == kModeAlpha || MODE == kModeSeedAlpha;
   constexpr bool BK = MODE == kModeBuckets || SD || AL;
+  constexpr bool QU = !SD && !DM;  // columns go through the queue
   constexpr int R2 = R * R;
+  constexpr int kUnits = unit_slots<MODE>();
   __shared__ double s_tab[kWaves][16 * kLdsRow + 2 * kTab2];
   __shared__ BucketEntry s_bucket[kWaves][65];  // entries NB..64: sinks of infeasible configurations
   __shared__ UnitRec s_unit[kWaves][kUnits];
   __shared__ float s_range[BK ? kWaves : 1][BK ? kRangeLevels * 64 : 1];
   __shared__ double s_ratio[2 * R];
+  __shared__ double s_qt[QU ? kWaves : 1][QU ? kQueue : 1];   // queued columns: their stable times
+  __shared__ uint32_t s_qi[QU ? kWaves : 1][QU ? kQueue : 1];  // and what they are
   __shared__ FiltEntry s_filt[EX ? kWaves : 1][EX ? 64 : 1];
   __shared__ double2 s_ab[AL ? kWaves : 1][kMaxAlphas];      // alpha * G, 1 - alpha
   __shared__ AlphaEntry s_aent[AL ? kWaves : 1][kMaxAlphas];
@@ -197,6 +206,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
     unsigned long long* const thr = a.thr ? a.thr + (size_t)tile.group * 64 : nullptr;
     unsigned long long* const athr = AL && a.athr ? a.athr + (size_t)tile.group * a.n_alpha : nullptr;
 
+    bool changed = false;  // some threshold fell since the tables below were formed
     // The range maxima of the thresholds, each rounded up to the next float (at least the smallest
     // normal one): still an upper bound.
     auto build_range = [&](unsigned long long key) {
@@ -271,6 +281,28 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
         build_alpha();
       }
     };
+    // The tables formed from the thresholds, after some fell.
+    auto refresh = [&]() {
+      wave_sync();
+      build_range(lds_load(&bucket[lane].key));
+      if constexpr (AL) build_alpha();
+      changed = false;
+    };
+    // A column's first-microbatch time T10 at the smallest optimizer ratio (host streams h0, d0), and the
+    // slope sl by which it grows at least.  Another optimizer ratio's is that time with both host
+    // streams longer by the same (r - r0) So / PCIe, and Algorithm 1's time is continuous and
+    // piecewise linear in that length, with no slope below slope0 (slope1 when GPU-GPU finishes first at
+    // the smallest ratio, slope2 when compute follows: as the host streams grow, it stays so).  With a
+    // negative slope the bound falls until it meets the host streams, which grow with slope 1.
+    [[maybe_unused]] auto first_times = [&](const KnownRow& fr, double C, double gf, int ia, double h0, double d0, bool free,
+                                            double& T10, double& sl) {
+      int f0 = kFormGeneral;
+      if (__builtin_amdgcn_ballot_w64((ia == 0) & !free))
+        T10 = interference(C, gf, h0, d0, tab);
+      else
+        T10 = interference_known(fr, h0, d0, free, tab, RK, f0);
+      sl = f0 == kFormGeneral ? slope0 : (f0 == kFormHostsLeft ? slope2 : slope1);
+    };
     // The largest objective that a configuration in the memory range [lo, hi] may have to matter.
     auto limit = [&](double lo, double hi) -> double {
       const unsigned int ja = (unsigned int)__builtin_fmin(lo * kLo, 63.0);
@@ -304,19 +336,263 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
       return may;
     };
 
+    // One strip: its unit's constants, weight and gradient ratios, and the levels they fix.
+    struct Strip {
+      OoIn I;
+      double HW, A, KA, A2, C, gs, gf;
+      int s;
+      bool zero;  // weight and gradient ratios 0
+    };
+    auto load_strip = [&](const UnitRec& U, int rem2) -> Strip {
+      const int iw = rem2 / R;
+      const int ig = rem2 - iw * R;
+      const double rw = s_ratio[iw], qw = s_ratio[R + iw], rg = s_ratio[ig], qg = s_ratio[R + ig];
+      const int z = U.unit & 3;
+      const double sw = z == 3 ? U.iD : 1.0, sg = z >= 2 ? U.iD : 1.0;
+      const double Sw = U.Pw * sw, Sg = U.Pw * sg;
+      Strip T;
+      T.I.So = U.So;
+      T.I.Swg = __builtin_fma(qg, Sg, qw * Sw);
+      T.I.Obo = U.Obo;
+      T.I.Og = rg * (U.Wb2 * sg);
+      T.I.DG = rg * Sg;
+      T.I.DW = rw * Sw;
+      T.I.Wbuf = U.Wb2 * (1.0 - qw * sw);
+      T.I.Gbuf = U.Wb2 * (1.0 - qg * sg);
+      T.I.Rc = U.ckpt ? 0.5 * U.A2 : 0.0;  // one layer's activations: 2A / 2, exactly
+      T.I.Xd = U.Xd;
+      T.HW = rw * (2.0 * Sw);
+      T.A = U.A;
+      T.KA = U.KA;
+      T.A2 = U.A2;
+      T.C = U.C;
+      T.gs = U.gs;
+      T.gf = U.gf;
+      T.s = U.unit * R2 + rem2;
+      T.zero = r0_zero && rw == 0.0 && rg == 0.0;
+      return T;
+    };
+    // A column's configurations: one optimizer ratio after the other, the lanes' columns side by side
+    // (strip T, activation ratio ia, host streams hs and ds, stash SO, stable time tv of each lane).  A
+    // lane takes part for the buckets (col) or the weight samples (acol).
+    auto configs = [&](const Strip& T, bool col, bool acol, int ia, double hs, double ds, double SO, double tv, int fst) {
+      const double C = T.C, gf = T.gf;
+      const double T1c = __builtin_fmax(C, gf);
+      const double Hx0 = __builtin_fma(ra0, T.I.So, T.I.DG) * iP, Dx0 = __builtin_fma(ra0, T.I.So, T.I.DW) * iP;
+      const KnownRow fr = known_row(tab, gf > 0.0 ? 15 : 13, C, gf);
+      const unsigned int lid_strip = (unsigned int)T.s * (unsigned int)R2;
+      // Weight samples: the column's first-microbatch time at the smallest optimizer ratio, with the
+      // slope by which it grows at least (first_times), and the limit of d.
+      [[maybe_unused]] double T10 = 0.0, sl = 0.0, dl = 0.0;
+      if constexpr (AL) {
+        first_times(fr, C, gf, ia, hs + Hx0, ds + Dx0, !(col | acol), T10, sl);
+        dl = d_limit(tv);
+      }
+#pragma unroll 1
+      for (int io = 0; io < R; ++io) {
+        const OoK O = oo_level(T.I, rr[io], om[io], iP);
+        const double hf = hs + O.H2Dx, df = ds + O.D2Hx;
+        const double mem = O.Bmax + SO;
+        // Bucket j = min{j : mem <= E_j}: floor(mem * kNB) is j or j - 1 (kNB carries a
+        // 2^-40 margin), so one comparison with E settles it.  An infeasible
+        // configuration (Eq. 4: mem > M = E_{NB-1}) has floor(mem * kNB) >= NB - 1 and
+        // lands on a sink: past NB - 1 the edges are +inf.  j0 = j - 1 needs mem within a
+        // relative 2^-40 above an edge, or an infeasible mem just above M: rare, so only
+        // entry j0's edge and key are read, and entry j0 + 1 (<= 64: entry 64's edge is
+        // +inf) only by lanes whose mem exceeds E_j0.
+        const int j0 = (int)__builtin_fmin(mem * kNB, 64.0);
+        const unsigned int off0 = __umul24((unsigned int)j0, (unsigned int)sizeof(BucketEntry));
+        char* const b0 = reinterpret_cast<char*>(bucket) + off0;
+        wave_sync();  // read the entry after every earlier update of the wave
+        const double e0 = reinterpret_cast<const BucketEntry*>(b0)->edge;
+        const unsigned long long k_lo = lds_load(&reinterpret_cast<const BucketEntry*>(b0)->key);
+        const bool up = mem > e0;
+        // The configuration's own bound against its bucket (a lane in entry j0 + 1 is kept).
+        bool may = col;
+        double T1b = __builtin_fmax(T1c, __builtin_fmax(hf, df));
+        if constexpr (AL) T1b = __builtin_fmax(T1b, __builtin_fma(sl, O.H2Dx - Hx0, T10));
+        const double lb = __builtin_fma(Gm1, tv, T1b);
+        [[maybe_unused]] bool amay = false;
+        if constexpr (EX) {
+          const double pm = *reinterpret_cast<const double*>(
+              reinterpret_cast<const char*>(s_filt[wave]) + __umul24((unsigned int)min(j0, 63), (unsigned int)sizeof(FiltEntry)));
+          may = may & (mem <= M) & (lb * lbs < pm);
+        } else if constexpr (BK) {
+          may = may & ((lb * lbs <= __longlong_as_double((long long)k_lo)) | up);
+          if constexpr (AL) {
+            amay = acol & (mem <= M) & (__builtin_fma(T1b, lbs, -tv) <= dl);
+            may = may | amay;
+          }
+        }
+        if (!__builtin_amdgcn_ballot_w64(may)) continue;
+        [[maybe_unused]] int f1 = 0;
+        const bool zero = (ia == 0) & (io == 0) & T.zero;
+        double T1 = interference_known(fr, hf, df, !may | zero, tab, RK, f1);
+        if (io == 0 && r0_zero) {  // a strip's all-zero configuration: no host streams
+          const double T1z = interference_zero(C, gf, tab);
+          T1 = zero ? T1z : T1;
+        }
+        const double d = T1 - tv;
+        const double obj = __builtin_fma(Gd, tv, d);
+        const unsigned int lid = lid_strip + (unsigned int)(io * R + ia);
+        if constexpr (DM) {
+          if (col) {
+            double* o = a.dump + kDumpWords * (a.dump_off[x] + (int64_t)(T.s - tile.strip_begin) * R2 + io * R + ia);
+            o[0] = tv;
+            o[1] = d;
+            o[2] = mem;
+            o[3] = obj;
+            o[4] = (double)(j0 + (up ? 1 : 0));
+            o[5] = (double)((zero ? kFormZero : f1) + 8 * fst);
+          }
+          continue;
+        }
+        if constexpr (EX) {
+          // Exact frontier candidates: feasible, below every lower bucket's minimum, and not
+          // dominated by the bucket's winner (no more memory and no smaller objective, not
+          // both equal).  Every frontier point passes; the scan after the sort decides.
+          const int j = min(j0 + (up ? 1 : 0), 63);
+          const FiltEntry f = s_filt[wave][j];
+          const bool cand = may & (obj < f.pm) &
+                            !(((obj > f.bobj) & (mem >= f.bmem)) | ((obj >= f.bobj) & (mem > f.bmem)));
+          const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
+          if (!m) continue;
+          int64_t slot = 0;
+          if (cand) {
+            const unsigned int below = __builtin_amdgcn_mbcnt_hi(
+                (unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+            slot = n_cand + below;
+            if (slot < n_end) {
+              a.cand_key[slot] = (unsigned long long)__double_as_longlong(mem);
+              a.cand_obj[slot] = obj;
+              a.cand_id[slot] = g.base + (uint64_t)lid;
+            }
+          }
+          // Past the window: the overflow pool, in chunks of kPoolChunk slots per wave (one
+          // device-wide atomic per chunk), else counted only and the tile is evaluated again.
+          const bool over = cand && slot >= n_end;
+          const unsigned long long mo = __builtin_amdgcn_ballot_w64(over);
+          if (mo && a.pool_count) {
+            const int k = __builtin_popcountll(mo);
+            if (pool_used + k > kPoolChunk) {
+              pool_holes(a, pool_base, pool_used, lane);
+              const int leader = __builtin_ctzll(mo);
+              unsigned long long b = 0;
+              if (lane == leader) b = atomicAdd(a.pool_count, (unsigned long long)kPoolChunk);
+              const unsigned long long bb = __shfl(b, leader, 64);
+              pool_base = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)(bb >> 32)) << 32) |
+                          (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)bb);
+              pool_used = 0;
+            }
+            if (over) {
+              const unsigned long long pos = pool_base + (unsigned long long)pool_used + __builtin_amdgcn_mbcnt_hi(
+                  (unsigned int)(mo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mo, 0u));
+              if (pos < (unsigned long long)a.pool_cap) {
+                a.pool_key[pos] = (unsigned long long)__double_as_longlong(mem);
+                a.pool_obj[pos] = obj;
+                a.pool_id[pos] = g.base + (uint64_t)lid;
+                a.pool_tile[pos] = t;
+                a.pool_rank[pos] = (int32_t)(slot - n_beg);
+              } else {
+                dropped = true;
+              }
+            }
+            pool_used += k;
+          } else if (mo) {
+            dropped = dropped | over;
+          }
+          n_cand += __builtin_popcountll(m);
+          continue;
+        }
+
+        // Lexicographic (obj, id) minimum per bucket without a serial loop: the lanes
+        // that beat their bucket's entry lower the objective bits with an LDS atomic
+        // minimum; a lane that sees its bucket's objective drop clears the id, then the
+        // lanes whose objective equals the new minimum lower the id.  The LDS operations
+        // of a wave execute in program order and each step addresses the same words as
+        // the one before, so each step sees the previous one's result.
+        const unsigned long long key = (unsigned long long)__double_as_longlong(obj);
+        if (__builtin_amdgcn_ballot_w64(may & ((key <= k_lo) | up))) {
+          BucketEntry* const be = reinterpret_cast<BucketEntry*>(b0 + (up ? sizeof(BucketEntry) : 0));
+          const unsigned long long k_old = up ? lds_load(&be->key) : k_lo;
+          const unsigned int i_old = lds_load(&be->lid);
+          const bool cand = may & ((key < k_old) | ((key == k_old) & (lid < i_old)));
+          changed = changed | (__builtin_amdgcn_ballot_w64(cand) != 0ull);
+          if (cand) atomicMin(&be->key, key);
+          const unsigned long long k_new = cand ? lds_load(&be->key) : 0ull;
+          if (cand && k_new < k_old) lds_store(&be->lid, 0xFFFFFFFFu);
+          if (cand && key == k_new) atomicMin(&be->lid, lid);
+        }
+        if constexpr (AL) {
+          // Eq. 4 for every weight sample, feasible configurations only: the samples some lane
+          // may win, each with the same three-step sequence on its single entry (the value's
+          // order key: weighted values may be negative).
+          amay = amay & (d <= dl);
+          if (__builtin_amdgcn_ballot_w64(amay)) {
+#pragma unroll 1
+            for (int q = 0; q < a.n_alpha; ++q) {
+              const double2 ab = s_ab[wave][q];
+              AlphaEntry* const e = &s_aent[wave][q];
+              const double v = __builtin_fma(ab.x, tv, ab.y * d);
+              const double cur = lds_load(&e->val);
+              if (!__builtin_amdgcn_ballot_w64(amay & (v <= cur))) continue;
+              const unsigned long long ak = order_key(v);
+              const unsigned long long ak_old = lds_load(&e->key);
+              const unsigned int ai_old = lds_load(&e->lid);
+              const bool cand = amay & ((ak < ak_old) | ((ak == ak_old) & (lid < ai_old)));
+              changed = changed | (__builtin_amdgcn_ballot_w64(cand) != 0ull);
+              if (cand) atomicMin(&e->key, ak);
+              const unsigned long long ak_new = cand ? lds_load(&e->key) : 0ull;
+              if (cand && ak_new < ak_old) lds_store(&e->lid, 0xFFFFFFFFu);
+              if (cand && ak == ak_new) {
+                atomicMin(&e->lid, lid);
+                lds_store(&e->val, v);
+              }
+              wave_sync();
+            }
+          }
+        }
+      }
+    };
+    // Queued columns, 64 at a time, a lane each: few lanes of a strip iteration reach this point (3 of 64
+    // on llama42b-d128-hw64), and side by side they share the optimizer level and the rounds.
+    int qn = 0;
+    auto flush = [&](int n) {
+      wave_sync();
+      const bool on = lane < n;
+      const uint32_t it = on ? s_qi[wave][qn - n + lane] : 0u;
+      const double tv = on ? s_qt[wave][qn - n + lane] : 0.0;
+      const int ia = (int)(it >> 13 & 15u);
+      const Strip T = load_strip(units[it & 31u], (int)(it >> 5 & 255u));
+      const double ra = s_ratio[ia], qa = s_ratio[R + ia];
+      const double hs = __builtin_fma(ra, T.A, T.HW) * iP, ds = __builtin_fma(ra, T.A, T.I.DG) * iP;
+      configs(T, on & ((it >> 17 & 1u) != 0u), on & ((it >> 18 & 1u) != 0u), ia, hs, ds,
+              __builtin_fma(ra, T.A2, qa * T.KA), tv, 0);
+      qn -= n;
+      if (BK && changed) refresh();
+    };
+
     const int nu = g.n_pairs * (l + 1) * 4;  // units of the group
-    // The tile's units in chunks of kUnits, one lane each.  A chunk takes one unit of each of kUnits
-    // equal segments, so that the first ones sample the whole tile and the thresholds settle early;
-    // the place within the segment turns with the lane, which mixes the ZeRO levels.  The seed
-    // variant samples one chunk over the whole group.
+    // The tile's units in chunks, one lane each.  A chunk takes one unit of each of kChunk equal
+    // segments, so that the first ones sample the whole tile and the thresholds settle early; the
+    // place within the segment turns with the lane, which mixes the ZeRO levels.  The first kUnits
+    // live ones are visited, then the others' bounds are taken again (the exact frontier's thresholds
+    // are final and few of its units live: it takes 64 at a time; with the buckets' a chunk of 64 tests
+    // too many units against early thresholds: 0.96 against 0.90 ms on llama7b-d32).  The seed variant
+    // samples one chunk over the whole group.
     const int u_beg = tile.strip_begin / R2;
     const int n_u = SD ? nu : (tile.strip_end > tile.strip_begin ? (tile.strip_end - 1) / R2 + 1 - u_beg : 0);
-    const int n_chunks = (n_u + kUnits - 1) / kUnits;
+    constexpr int kChunk = EX ? 64 : kUnits;
+    const int n_chunks = (n_u + kChunk - 1) / kChunk;
     for (int k = 0; k < (SD ? 1 : n_chunks); ++k) {
-      if constexpr (BK) exchange(k > 0);
       const int at = (k + lane) % n_chunks + n_chunks * lane;
       const int u = u_beg + at;
-      bool live = lane < kUnits && at < n_u;
+      bool pending = lane < kChunk && at < n_u;
+      bool again = k > 0;
+      while (__builtin_amdgcn_ballot_w64(pending)) {
+      if constexpr (BK) exchange(again);
+      again = true;
+      bool live = pending;
       UnitRec rec{};
       if (live) {
         const int uc = u >> 2, z = u & 3;
@@ -325,8 +601,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
         const PairK P = pk[g.pk_begin + p];
         const CkptK K = ckpt_level(P, l, c, ke);
         const ZeroK Z = zero_level(P, z);
-        rec = UnitRec{Z.Sw, Z.Sg, Z.sw, Z.sg, P.Wb2, Z.Obg, Z.So, Z.Obo, K.Rc, P.Xd,
-                      K.A, K.KA, P.A2, K.C, Z.G2Gs, Z.G2Gf, u, 0};
+        rec = UnitRec{P.Pw, P.iD, P.Wb2, Z.So, Z.Obo, P.Xd, K.A, K.KA, P.A2, K.C, Z.G2Gs, Z.G2Gf, u, c > 0 ? 1 : 0};
         if constexpr (!DM && !SD) {
           // End values of each ratio's terms: weights (both peaks), gradients and optimizer states
           // (forward peak, backward peak), activations.
@@ -350,23 +625,25 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
         }
       }
       const unsigned long long lm = __builtin_amdgcn_ballot_w64(live);
-      const int n_live = __builtin_popcountll(lm);
+      const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(lm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)lm, 0u));
+      const int n_live = min(__builtin_popcountll(lm), kUnits);
       any_live = any_live | (n_live > 0);
+      pending = live & (rank >= kUnits);
       wave_sync();  // the previous units' records are done with
-      if (live)
-        units[__builtin_amdgcn_mbcnt_hi((unsigned int)(lm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)lm, 0u))] = rec;
+      if (live & (rank < kUnits)) units[rank] = rec;
       wave_sync();
 
-      // Strips of the live units, one lane each, 64 at a time.
+      // Strips of the live units, one lane each, 64 at a time, and whenever the queue holds 64 columns
+      // (or at the end some) those: the strips' values are not kept across that but formed again, so
+      // that neither part holds the other's registers.
       const int n_strips = SD ? 64 * kSeedIters : n_live * R2;
-      bool changed = false;  // some bucket's minimum fell since the range maxima were formed
-      for (int i0 = 0; i0 < n_strips; i0 += 64) {
-        if (BK && changed) {
-          wave_sync();
-          build_range(lds_load(&bucket[lane].key));
-          if constexpr (AL) build_alpha();
-          changed = false;
+      int i0 = 0, ca = 0;  // strips done, columns done of the next ones
+      while (i0 < n_strips || qn > 0) {
+        if (QU && (qn >= 64 || i0 >= n_strips)) {
+          flush(min(qn, 64));
+          continue;
         }
+        if (BK && changed) refresh();
         const int i = i0 + lane;
         int slot, rem2;
         bool on;
@@ -380,38 +657,25 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
           on = i < n_strips;
         }
         slot = on ? slot : 0;
-        const UnitRec& U = units[slot];
-        const int s = U.unit * R2 + rem2;
-        if constexpr (!SD) on = on & (s >= tile.strip_begin) & (s < tile.strip_end);
-        const int iw = rem2 / R;
-        const int ig = rem2 - iw * R;
-        const double rw = s_ratio[iw], qw = s_ratio[R + iw], rg = s_ratio[ig], qg = s_ratio[R + ig];
-        const double So = U.So, Obo = U.Obo, Rc = U.Rc, Xd = U.Xd;
-        const double Wbuf = U.Wb2 * (1.0 - qw * U.sw);
-        const double Swg = __builtin_fma(qg, U.Sg, qw * U.Sw);
-        const double Gbuf = U.Wb2 * (1.0 - qg * U.sg);
-        const double HW = rw * (2.0 * U.Sw), DW = rw * U.Sw, DG = rg * U.Sg, Og = rg * U.Obg;
-        const double A = U.A, KA = U.KA, A2 = U.A2, C = U.C, gs = U.gs, gf = U.gf;
-        const OoIn I{So, Swg, Obo, Og, DG, DW, Wbuf, Gbuf, Rc, Xd};
+        const Strip T = load_strip(units[slot], rem2);
+        if constexpr (!SD) on = on & (T.s >= tile.strip_begin) & (T.s < tile.strip_end);
+        const double A = T.A, KA = T.KA, A2 = T.A2, C = T.C, gs = T.gs, gf = T.gf, HW = T.HW, DG = T.I.DG;
         // Peak without the activation terms over the optimizer ratios: between Blo and Bhi.
         double Blo, Bhi;
         {
-          const double b0 = __builtin_fma(qa0, So, Swg) + Wbuf, b1 = __builtin_fma(qa1, So, Swg) + Wbuf;
-          const double f0 = b0 + __builtin_fma(ra0, Obo, Og), f1 = b1 + __builtin_fma(ra1, Obo, Og);
-          const double g0 = (b0 + Gbuf) + Rc, g1 = (b1 + Gbuf) + Rc;
-          Blo = __builtin_fmax(__builtin_fmin(f0, f1), g1) + Xd;
-          Bhi = __builtin_fmax(__builtin_fmax(f0, f1), g0) + Xd;
+          const OoIn& I = T.I;
+          const double b0 = __builtin_fma(qa0, I.So, I.Swg) + I.Wbuf, b1 = __builtin_fma(qa1, I.So, I.Swg) + I.Wbuf;
+          const double f0 = b0 + __builtin_fma(ra0, I.Obo, I.Og), f1 = b1 + __builtin_fma(ra1, I.Obo, I.Og);
+          const double g0 = (b0 + I.Gbuf) + I.Rc, g1 = (b1 + I.Gbuf) + I.Rc;
+          Blo = __builtin_fmax(__builtin_fmin(f0, f1), g1) + I.Xd;
+          Bhi = __builtin_fmax(__builtin_fmax(f0, f1), g0) + I.Xd;
         }
-        const double Hx0 = __builtin_fma(ra0, So, DG) * iP, Dx0 = __builtin_fma(ra0, So, DW) * iP;
+        const double Hx0 = __builtin_fma(ra0, T.I.So, DG) * iP, Dx0 = __builtin_fma(ra0, T.I.So, T.I.DW) * iP;
         const double tc = __builtin_fmax(C, gs), T1c = __builtin_fmax(C, gf);
-        const bool zero_strip = r0_zero && rw == 0.0 && rg == 0.0;
-        const unsigned int lid_strip = (unsigned int)s * (unsigned int)R2;
-        // Both calls' first rounds.  With a positive activation ratio both host streams run, so the
-        // stable microbatch's first round has the pattern compute, both host streams, and GPU-GPU
-        // when it carries traffic; the first microbatch's configurations with a non-zero offload
-        // ratio start likewise.
+        // With a positive activation ratio both host streams run, so the stable microbatch's first
+        // round has the pattern compute, both host streams, and GPU-GPU when it carries traffic; the
+        // first microbatch's configurations with a non-zero offload ratio start likewise.
         const KnownRow sr = known_row(tab, gs > 0.0 ? 15 : 13, C, gs);
-        const KnownRow fr = known_row(tab, gf > 0.0 ? 15 : 13, C, gf);
         // Weight samples: whether the strip may matter to one, the largest d with which it may, and
         // whether it may matter to a bucket (few strips do: the others' columns skip that test).
         [[maybe_unused]] bool smp = false, bkt = true;
@@ -425,12 +689,17 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
           on = on & (lo <= Mhi);
           smp = sample_alive(tl, T1l);
           bkt = __builtin_amdgcn_ballot_w64(on & alive(lo, __builtin_fma(Gm1, tl, T1l), limit(lo, hi))) != 0ull;
-          if (!bkt & !__builtin_amdgcn_ballot_w64(on & smp)) continue;
+          if (!bkt & !__builtin_amdgcn_ballot_w64(on & smp)) {  // nothing in these strips
+            ca = 0;
+            i0 += 64;
+            continue;
+          }
           dls = d_limit(tl * lbs);
         }
 
 #pragma unroll 1
-        for (int ia = 0; ia < R; ++ia) {
+        for (; ca < R && qn < 64; ++ca) {
+          const int ia = ca;
           const double ra = rr[ia], qa = om[ia];
           const double hs = __builtin_fma(ra, A, HW) * iP;
           const double ds = __builtin_fma(ra, A, DG) * iP;
@@ -455,199 +724,39 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
           col = col & alive(Blo + SO, __builtin_fma(Gm1, tv, T1l), th);
           if constexpr (AL) acol = acol & (__builtin_fma(T1l, lbs, -tv) <= dls);
           if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
-          // Weight samples: the column's first-microbatch time T10 at the smallest optimizer ratio
-          // bounds the others'.  Each is that time with both host streams longer by the same
-          // (r - r0) So / PCIe, and Algorithm 1's time is continuous and piecewise linear in that
-          // length, with no slope below slope0 (slope1 when GPU-GPU finishes first at the smallest
-          // ratio, slope2 when compute follows: as the host streams grow, it stays so).  With a
-          // negative slope the bound falls until it meets the host streams, which grow with slope 1.
+          // Weight samples: the first-microbatch time at the smallest optimizer ratio bounds the column's.
           // (For the buckets alone it excludes too little for its cost: 6.4 against 5.7 ms on
           // llama42b-d128-hw64.)
-          [[maybe_unused]] double T10 = 0.0, sl = 0.0, dl = 0.0;
           if constexpr (AL) {
-            int f0 = kFormGeneral;
+            const KnownRow fr = known_row(tab, gf > 0.0 ? 15 : 13, C, gf);
+            double T10, sl;
             const double h0 = hs + Hx0, d0 = ds + Dx0;
-            if (ia == 0)
-              T10 = interference(C, gf, h0, d0, tab);
-            else
-              T10 = interference_known(fr, h0, d0, !(col | acol), tab, RK, f0);
-            sl = f0 == kFormGeneral ? slope0 : (f0 == kFormHostsLeft ? slope2 : slope1);
+            first_times(fr, C, gf, ia, h0, d0, !(col | acol), T10, sl);
             const double neg = __builtin_fmin(sl, 0.0);
             const double T1m = __builtin_fmax(T1l, T10 + neg * (1.0 / (1.0 - neg)) * (T10 - __builtin_fmax(h0, d0)));
             col = col & alive(Blo + SO, __builtin_fma(Gm1, tv, T1m), th);
             acol = acol & (__builtin_fma(T1m, lbs, -tv) <= dls);
             if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
-            dl = d_limit(tv);
-            acol = acol & (__builtin_fma(T1m, lbs, -tv) <= dl);
-            if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
+            acol = acol & (__builtin_fma(T1m, lbs, -tv) <= d_limit(tv));
           }
-
-#pragma unroll 1
-          for (int io = 0; io < R; ++io) {
-            const OoK O = oo_level(I, rr[io], om[io], iP);
-            const double hf = hs + O.H2Dx, df = ds + O.D2Hx;
-            const double mem = O.Bmax + SO;
-            // Bucket j = min{j : mem <= E_j}: floor(mem * kNB) is j or j - 1 (kNB carries a
-            // 2^-40 margin), so one comparison with E settles it.  An infeasible
-            // configuration (Eq. 4: mem > M = E_{NB-1}) has floor(mem * kNB) >= NB - 1 and
-            // lands on a sink: past NB - 1 the edges are +inf.  j0 = j - 1 needs mem within a
-            // relative 2^-40 above an edge, or an infeasible mem just above M: rare, so only
-            // entry j0's edge and key are read, and entry j0 + 1 (<= 64: entry 64's edge is
-            // +inf) only by lanes whose mem exceeds E_j0.
-            const int j0 = (int)__builtin_fmin(mem * kNB, 64.0);
-            const unsigned int off0 = __umul24((unsigned int)j0, (unsigned int)sizeof(BucketEntry));
-            char* const b0 = reinterpret_cast<char*>(bucket) + off0;
-            wave_sync();  // read the entry after every earlier update of the wave
-            const double e0 = reinterpret_cast<const BucketEntry*>(b0)->edge;
-            const unsigned long long k_lo = lds_load(&reinterpret_cast<const BucketEntry*>(b0)->key);
-            const bool up = mem > e0;
-            // The configuration's own bound against its bucket (a lane in entry j0 + 1 is kept).
-            bool may = col;
-            double T1b = __builtin_fmax(T1c, __builtin_fmax(hf, df));
-            if constexpr (AL) T1b = __builtin_fmax(T1b, __builtin_fma(sl, O.H2Dx - Hx0, T10));
-            const double lb = __builtin_fma(Gm1, tv, T1b);
-            [[maybe_unused]] bool amay = false;
-            if constexpr (EX) {
-              const double pm = *reinterpret_cast<const double*>(
-                  reinterpret_cast<const char*>(s_filt[wave]) + __umul24((unsigned int)min(j0, 63), (unsigned int)sizeof(FiltEntry)));
-              may = may & (mem <= M) & (lb * lbs < pm);
-            } else if constexpr (BK) {
-              may = may & ((lb * lbs <= __longlong_as_double((long long)k_lo)) | up);
-              if constexpr (AL) {
-                amay = acol & (mem <= M) & (__builtin_fma(T1b, lbs, -tv) <= dl);
-                may = may | amay;
-              }
+          const unsigned long long m = __builtin_amdgcn_ballot_w64(col | acol);
+          if (!m) continue;
+          if constexpr (QU) {
+            if (col | acol) {
+              const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+              s_qt[wave][pos] = tv;
+              s_qi[wave][pos] = (uint32_t)slot | (uint32_t)rem2 << 5 | (uint32_t)ia << 13 | (col ? 1u << 17 : 0u) | (acol ? 1u << 18 : 0u);
             }
-            if (!__builtin_amdgcn_ballot_w64(may)) continue;
-            [[maybe_unused]] int f1 = 0;
-            const bool zero = ia == 0 && io == 0 && zero_strip;
-            double T1 = interference_known(fr, hf, df, !may | zero, tab, RK, f1);
-            if (ia == 0 && io == 0) {  // the strip's all-zero configuration: no host streams
-              const double T1z = interference_zero(C, gf, tab);
-              T1 = zero ? T1z : T1;
-            }
-            const double d = T1 - tv;
-            const double obj = __builtin_fma(Gd, tv, d);
-            const unsigned int lid = lid_strip + (unsigned int)(io * R + ia);
-            if constexpr (DM) {
-              if (on) {
-                double* o = a.dump + kDumpWords * (a.dump_off[x] + (int64_t)(s - tile.strip_begin) * R2 + io * R + ia);
-                o[0] = tv;
-                o[1] = d;
-                o[2] = mem;
-                o[3] = obj;
-                o[4] = (double)(j0 + (up ? 1 : 0));
-                o[5] = (double)((zero ? kFormZero : f1) + 8 * fst);
-              }
-              continue;
-            }
-            if constexpr (EX) {
-              // Exact frontier candidates: feasible, below every lower bucket's minimum, and not
-              // dominated by the bucket's winner (no more memory and no smaller objective, not
-              // both equal).  Every frontier point passes; the scan after the sort decides.
-              const int j = min(j0 + (up ? 1 : 0), 63);
-              const FiltEntry f = s_filt[wave][j];
-              const bool cand = may & (obj < f.pm) &
-                                !(((obj > f.bobj) & (mem >= f.bmem)) | ((obj >= f.bobj) & (mem > f.bmem)));
-              const unsigned long long m = __builtin_amdgcn_ballot_w64(cand);
-              if (!m) continue;
-              int64_t slot = 0;
-              if (cand) {
-                const unsigned int below = __builtin_amdgcn_mbcnt_hi(
-                    (unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
-                slot = n_cand + below;
-                if (slot < n_end) {
-                  a.cand_key[slot] = (unsigned long long)__double_as_longlong(mem);
-                  a.cand_obj[slot] = obj;
-                  a.cand_id[slot] = g.base + (uint64_t)lid;
-                }
-              }
-              // Past the window: the overflow pool, in chunks of kPoolChunk slots per wave (one
-              // device-wide atomic per chunk), else counted only and the tile is evaluated again.
-              const bool over = cand && slot >= n_end;
-              const unsigned long long mo = __builtin_amdgcn_ballot_w64(over);
-              if (mo && a.pool_count) {
-                const int k = __builtin_popcountll(mo);
-                if (pool_used + k > kPoolChunk) {
-                  pool_holes(a, pool_base, pool_used, lane);
-                  const int leader = __builtin_ctzll(mo);
-                  unsigned long long b = 0;
-                  if (lane == leader) b = atomicAdd(a.pool_count, (unsigned long long)kPoolChunk);
-                  const unsigned long long bb = __shfl(b, leader, 64);
-                  pool_base = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)(bb >> 32)) << 32) |
-                              (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)bb);
-                  pool_used = 0;
-                }
-                if (over) {
-                  const unsigned long long pos = pool_base + (unsigned long long)pool_used + __builtin_amdgcn_mbcnt_hi(
-                      (unsigned int)(mo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mo, 0u));
-                  if (pos < (unsigned long long)a.pool_cap) {
-                    a.pool_key[pos] = (unsigned long long)__double_as_longlong(mem);
-                    a.pool_obj[pos] = obj;
-                    a.pool_id[pos] = g.base + (uint64_t)lid;
-                    a.pool_tile[pos] = t;
-                    a.pool_rank[pos] = (int32_t)(slot - n_beg);
-                  } else {
-                    dropped = true;
-                  }
-                }
-                pool_used += k;
-              } else if (mo) {
-                dropped = dropped | over;
-              }
-              n_cand += __builtin_popcountll(m);
-              continue;
-            }
-
-            // Lexicographic (obj, id) minimum per bucket without a serial loop: the lanes
-            // that beat their bucket's entry lower the objective bits with an LDS atomic
-            // minimum; a lane that sees its bucket's objective drop clears the id, then the
-            // lanes whose objective equals the new minimum lower the id.  The LDS operations
-            // of a wave execute in program order and each step addresses the same words as
-            // the one before, so each step sees the previous one's result.
-            const unsigned long long key = (unsigned long long)__double_as_longlong(obj);
-            if (__builtin_amdgcn_ballot_w64(may & ((key <= k_lo) | up))) {
-              BucketEntry* const be = reinterpret_cast<BucketEntry*>(b0 + (up ? sizeof(BucketEntry) : 0));
-              const unsigned long long k_old = up ? lds_load(&be->key) : k_lo;
-              const unsigned int i_old = lds_load(&be->lid);
-              const bool cand = may & ((key < k_old) | ((key == k_old) & (lid < i_old)));
-              changed = changed | (__builtin_amdgcn_ballot_w64(cand) != 0ull);
-              if (cand) atomicMin(&be->key, key);
-              const unsigned long long k_new = cand ? lds_load(&be->key) : 0ull;
-              if (cand && k_new < k_old) lds_store(&be->lid, 0xFFFFFFFFu);
-              if (cand && key == k_new) atomicMin(&be->lid, lid);
-            }
-            if constexpr (AL) {
-              // Eq. 4 for every weight sample, feasible configurations only: the samples some lane
-              // may win, each with the same three-step sequence on its single entry (the value's
-              // order key: weighted values may be negative).
-              amay = amay & (d <= dl);
-              if (__builtin_amdgcn_ballot_w64(amay)) {
-#pragma unroll 1
-                for (int q = 0; q < a.n_alpha; ++q) {
-                  const double2 ab = s_ab[wave][q];
-                  AlphaEntry* const e = &s_aent[wave][q];
-                  const double v = __builtin_fma(ab.x, tv, ab.y * d);
-                  const double cur = lds_load(&e->val);
-                  if (!__builtin_amdgcn_ballot_w64(amay & (v <= cur))) continue;
-                  const unsigned long long ak = order_key(v);
-                  const unsigned long long ak_old = lds_load(&e->key);
-                  const unsigned int ai_old = lds_load(&e->lid);
-                  const bool cand = amay & ((ak < ak_old) | ((ak == ak_old) & (lid < ai_old)));
-                  changed = changed | (__builtin_amdgcn_ballot_w64(cand) != 0ull);
-                  if (cand) atomicMin(&e->key, ak);
-                  const unsigned long long ak_new = cand ? lds_load(&e->key) : 0ull;
-                  if (cand && ak_new < ak_old) lds_store(&e->lid, 0xFFFFFFFFu);
-                  if (cand && ak == ak_new) {
-                    atomicMin(&e->lid, lid);
-                    lds_store(&e->val, v);
-                  }
-                  wave_sync();
-                }
-              }
-            }
+            qn += __builtin_popcountll(m);
+          } else {
+            configs(T, col, acol, ia, hs, ds, SO, tv, fst);
           }
         }
+        if (ca == R) {
+          ca = 0;
+          i0 += 64;
+        }
+      }
       }
     }
     if constexpr (SD) {
