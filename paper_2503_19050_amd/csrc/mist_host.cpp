@@ -44,11 +44,11 @@ constexpr int64_t kStaticStrips = 512;        // strips per resident wave up to 
                                               // cut into one tile per wave
 constexpr int64_t kMinTileConfigs = 16384;    // configurations per tile of a larger space, at least
 constexpr int64_t kMinBoundedConfigs = 32768; // the same in the bounded search
-constexpr int64_t kTilesPerWave = 4;          // full-size tiles per resident wave there, at most about
+constexpr int64_t kTilesPerWave = 12;         // full-size tiles per resident wave there, at most about
 // Spaces that the bounded search evaluates: enough configurations that the bounds exclude more than
 // they cost, and large enough groups (use_bounds).
 constexpr uint64_t kBoundedConfigs = 120000000, kBoundedPerGroup = 8000;
-constexpr uint64_t kBoundedAlphaConfigs = 250000000, kBoundedAlphaPerGroup = 30000;
+constexpr uint64_t kBoundedAlphaConfigs = 450000000, kBoundedAlphaPerGroup = 30000;
 constexpr int64_t kMaxTiles = 131072;         // and tiles per space, at most
 constexpr int64_t kWindowDiv = 8;             // exact frontier: candidate window of a tile,
                                               // 1/kWindowDiv of its configurations
@@ -669,8 +669,9 @@ namespace {
 // spaces of 1e6 to 3e9 configurations (evaluation kernel, every configuration / bounded search): with
 // buckets alone 0.5-1.1x below 1e8, 1.2-1.9x from 1.2e8 to 3e8, 2-12x above 6e8; below about 8,000
 // configurations per group the tables and the seeds of a group cost more than its bounds save
-// (0.55x at 1,500, 0.97x at 8,400).  With weight samples, whose smallest delta is hard to bound, 0.5-1.0x
-// below 2.5e8 or about 30,000 configurations per group (0.88x at 21,000), 1.2-2.2x above.
+// (0.55x at 1,500, 0.97x at 8,400).  With weight samples, whose smallest delta is hard to bound, 0.65-1.1x
+// from 2.5e8 to 4.5e8 (mean 0.85x), 1.1-2.6x above (mean 1.4x; 0.92x and 0.97x in two of 35 spaces, of 2 and
+// 4 devices), and 0.85-0.93x in groups of fewer than about 30,000.
 bool use_bounds(const mist_space* S) {
   const uint64_t n = S->n_configs, g = (uint64_t)S->groups.size();
   if (S->A > 0) return g > 0 && n >= kBoundedAlphaConfigs && n / g >= kBoundedAlphaPerGroup;
@@ -701,7 +702,13 @@ uint64_t tile_strips(const mist_space* S, uint64_t total_strips, int64_t residen
 // at most kStaticStrips strips per resident wave is cut into about one tile per resident wave,
 // so that no claim is made.  A larger one is cut into tiles of at least the space's
 // tile_configs configurations (kMinTileConfigs unless the descriptor asks for another size;
-// claims on one counter serialize) and at most kMaxTiles tiles; the last
+// claims on one counter serialize) and at most kMaxTiles tiles.  The bounded search's default is
+// kMinBoundedConfigs, or what makes about kTilesPerWave full-size tiles per resident wave: a tile
+// starts from its group's thresholds, which its first units and the tiles before it sharpen
+// (build_tile_order), while few tiles leave waves idle at the end.  Measured, ms: 4, 12 and 32 tiles per
+// wave give 2.08, 2.07 and 1.84 on llama13b-d64, 0.88, 0.80 and 0.82 on llama7b-d32, 3.90, 3.82 and
+// 3.87 on llama42b-d128-hw64, and with weight samples on llama7b-d32 3.34, 3.42 and 3.84; tiles of 16,384,
+// 32,768 and 65,536 configurations 0.43, 0.40 and 0.41 on gpt2.7b-d16 (before the queue).  The last
 // kTailPercent percent of a group's strips (rounded up to its last full-size tile) go into
 // tiles a quarter of that size, placed after all full-size tiles, so that the waves that
 // finish last wait for a small tile.
@@ -796,11 +803,22 @@ std::string build_tile_order(mist_space* S, int64_t n_waves, int32_t n_full) {
     sc[x] = cum - fc[x];
     if (x < kClaimCounters) cum += cnt[x];
   }
+  // The bounded search takes an XCD's first tile of every group, then its second ones, and so on: by
+  // then the first has lowered the group's thresholds (llama42b-d128-hw64 4.32 -> 3.90 ms, llama13b-d64
+  // 2.30 -> 2.08, with weight samples 9.9 -> 9.7 and 21.7 -> 20.3).
+  std::vector<int32_t> full((size_t)n_full);
+  for (int32_t i = 0; i < n_full; ++i) full[(size_t)i] = i;
+  if (S->bounded)
+    for (int x = 0; x < kClaimCounters; ++x)
+      std::stable_sort(full.begin() + fc[x], full.begin() + fc[x + 1], [&](int32_t a, int32_t b) {
+        const auto rank = [&](int32_t t) { return t - S->groups[(size_t)S->tiles[(size_t)t].group].tile_begin; };
+        return rank(a) < rank(b);
+      });
   int64_t pos[kClaimCounters] = {};
   const auto next = [&](int x) -> int32_t {
     const int64_t k = pos[x]++;
     const int64_t nf = fc[x + 1] - fc[x];
-    return (int32_t)(k < nf ? fc[x] + k : n_full + sc[x] + (k - nf));
+    return (int32_t)(k < nf ? full[(size_t)(fc[x] + k)] : n_full + sc[x] + (k - nf));
   };
   for (int64_t i = 0; i < n_waves; ++i) S->tile_order[(size_t)i] = next((int)((i / kWaves) % kClaimCounters));
   for (int64_t i = n_waves; i < n; ++i) S->tile_order[(size_t)i] = next((int)((i - n_waves) % kClaimCounters));
