@@ -216,6 +216,9 @@ mist_status mist_eval_space(mist_space* S, void* hip_stream);
  * candidate stage: waits for the last evaluation and writes, for groups g0..g0+n-1, the
  * feasible configuration of minimum obj (lowest id among equal obj) into host out[0..n-1]; a
  * group without a feasible configuration gets id MIST_NONE, obj +inf, bucket -1.
+ * Every call that reads results waits for the stream of the call that formed them, then reads on
+ * the null stream of the space's device: the replay of a captured evaluation is read after it runs
+ * when it was launched on the null stream or a blocking stream.
  * Errors: MIST_E_STATE (no evaluation yet), MIST_E_RANGE, MIST_E_DEVICE. */
 mist_status mist_get_best(mist_space* S, int64_t g0, int64_t n, mist_result* out);
 

@@ -625,36 +625,63 @@ mist_status eval_ids_impl(mist_space* S, const uint64_t* ids, int64_t n, double*
   return MIST_OK;
 }
 
+// The reads of results (fetch, fetch_results and their kernels) run on the null stream of the space's
+// device, behind the call that formed them: its stream is waited for here, and what the caller has
+// queued on the null stream or on any blocking stream since, such as the replay of a captured
+// evaluation, comes first by the null stream's own order.  Returns with the space's device current
+// while `on` lives.
+struct OnDevice {
+  int prev = -1;
+  ~OnDevice() {
+    if (prev >= 0) (void)hipSetDevice(prev);
+  }
+  hipError_t enter(int device) {
+    int cur = device;
+    hipError_t e = hipGetDevice(&cur);
+    if (e == hipSuccess && cur != device) {
+      e = hipSetDevice(device);
+      if (e == hipSuccess) prev = cur;
+    }
+    return e;
+  }
+};
+
+mist_status begin_reads(const mist_space* S, hipStream_t after, OnDevice* on) {
+  hipError_t e = on->enter(S->device);
+  if (e == hipSuccess && after) e = hipStreamSynchronize(after);
+  return e == hipSuccess ? MIST_OK : fail_hip(e, "hipStreamSynchronize");
+}
+
 // The space's device workspace of at least `bytes`, kept for later calls.  Every call that uses it
 // waits for its own work before it returns.
-void* workspace(mist_space* S, size_t bytes, hipStream_t st) {
+void* workspace(mist_space* S, size_t bytes) {
   if (bytes > S->ws_bytes) {
     dev_free_one(S, S->d_ws);
     S->ws_bytes = 0;
-    S->d_ws = dev_alloc(S, bytes, st);
+    S->d_ws = dev_alloc(S, bytes, nullptr);
     if (S->d_ws) S->ws_bytes = bytes;
   }
   return S->d_ws;
 }
 
-// Copies back what the stream's work leaves at src and waits.
-mist_status fetch(void* dst, const void* src, size_t bytes, hipStream_t st, const char* what) {
-  hipError_t e = copy_async(dst, src, bytes, hipMemcpyDeviceToHost, st);
-  const hipError_t w = hipStreamSynchronize(st);
+// Copies back what the null stream's work leaves at src and waits.
+mist_status fetch(void* dst, const void* src, size_t bytes, const char* what) {
+  hipError_t e = copy_async(dst, src, bytes, hipMemcpyDeviceToHost, nullptr);
+  const hipError_t w = hipStreamSynchronize(nullptr);
   if (e == hipSuccess) e = w;
   return e == hipSuccess ? MIST_OK : fail_hip(e, what);
 }
 
 // Results of n configurations whose ids and objectives (with n_alpha > 0: weighted values) lie on the
-// device, formed there behind the work queued on st.
+// device, formed there.
 mist_status fetch_results(mist_space* S, const uint64_t* ids, const double* objs, const uint64_t* key, int32_t n_alpha,
-                          int64_t n, mist_result* out, hipStream_t st) {
+                          int64_t n, mist_result* out) {
   if (n == 0) return MIST_OK;
-  mist_result* w = (mist_result*)workspace(S, (size_t)n * sizeof(mist_result), st);
+  mist_result* w = (mist_result*)workspace(S, (size_t)n * sizeof(mist_result));
   if (!w) return fail(MIST_E_NOMEM, "device allocation failed: results");
-  const int k = launch_results(eval_args(S), ids, objs, key, n_alpha, n, w, st);
+  const int k = launch_results(eval_args(S), ids, objs, key, n_alpha, n, w, nullptr);
   if (k) return fail_hip((hipError_t)k, "results launch");
-  const mist_status rc = fetch(out, w, (size_t)n * sizeof(mist_result), st, "results");
+  const mist_status rc = fetch(out, w, (size_t)n * sizeof(mist_result), "results");
   if (rc) return rc;
   for (int64_t i = 0; i < n; ++i)
     if (out[i].pad) return fail(MIST_E_DEVICE, "re-evaluated configuration differs");
@@ -1331,10 +1358,13 @@ mist_status mist_get_pareto_exact(mist_space* S, int64_t g, mist_result* out, in
   if (!S || !n_out || (!out && cap > 0)) return fail(MIST_E_INVALID, "null argument");
   if (!S->exact_done) return fail(MIST_E_STATE, "mist_eval_pareto_exact has not been called");
   if (g < 0 || g >= (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group out of range");
+  OnDevice on;
+  mist_status rc = begin_reads(S, S->exact_stream, &on);
+  if (rc) return rc;
   try {
     if (S->front_cnt.empty()) {  // every group's count comes back with the first
       std::vector<int64_t> cnt(S->groups.size());
-      const mist_status rc = fetch(cnt.data(), S->d_front_cnt, cnt.size() * sizeof(int64_t), S->exact_stream, "frontier counts");
+      rc = fetch(cnt.data(), S->d_front_cnt, cnt.size() * sizeof(int64_t), "frontier counts");
       if (rc) return rc;
       S->front_cnt.swap(cnt);
     }
@@ -1342,7 +1372,7 @@ mist_status mist_get_pareto_exact(mist_space* S, int64_t g, mist_result* out, in
     *n_out = n;
     if (n > cap) return fail(MIST_E_RANGE, "cap is smaller than the frontier");
     const size_t b = (size_t)S->h_seg[g];
-    return fetch_results(S, S->d_front_id + b, S->d_front_obj + b, S->d_front_key + b, 0, n, out, S->exact_stream);
+    return fetch_results(S, S->d_front_id + b, S->d_front_obj + b, S->d_front_key + b, 0, n, out);
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1351,10 +1381,13 @@ mist_status mist_get_pareto_exact(mist_space* S, int64_t g, mist_result* out, in
 mist_status mist_get_best(mist_space* S, int64_t g0, int64_t n, mist_result* out) {
   if (!S || (!out && n > 0)) return fail(MIST_E_INVALID, "null argument");
   if (g0 < 0 || n < 0 || g0 + n > (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group range");
-  const mist_status rc = n == 0 ? wait_results(S) : have_results(S);
+  mist_status rc = n == 0 ? wait_results(S) : have_results(S);
   if (rc || n == 0) return rc;
+  OnDevice on;
+  rc = begin_reads(S, S->stream, &on);
+  if (rc) return rc;
   try {
-    return fetch_results(S, S->d_best_id + g0, S->d_best_obj + g0, nullptr, 0, n, out, S->stream);
+    return fetch_results(S, S->d_best_id + g0, S->d_best_obj + g0, nullptr, 0, n, out);
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1364,11 +1397,14 @@ mist_status mist_get_alpha(mist_space* S, int64_t g0, int64_t n, mist_result* ou
   if (!S || (!out && n > 0)) return fail(MIST_E_INVALID, "null argument");
   if (S->A == 0) return fail(MIST_E_STATE, "the space has no weight samples");
   if (g0 < 0 || n < 0 || g0 + n > (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group range");
-  const mist_status rc = n == 0 ? wait_results(S) : have_results(S);
+  mist_status rc = n == 0 ? wait_results(S) : have_results(S);
   if (rc || n == 0) return rc;
+  OnDevice on;
+  rc = begin_reads(S, S->stream, &on);
+  if (rc) return rc;
   try {
     const size_t at = (size_t)g0 * (size_t)S->A;
-    return fetch_results(S, S->d_alpha_id + at, S->d_alpha_obj + at, nullptr, S->A, n * S->A, out, S->stream);
+    return fetch_results(S, S->d_alpha_id + at, S->d_alpha_obj + at, nullptr, S->A, n * S->A, out);
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
   }
@@ -1379,6 +1415,8 @@ mist_status mist_plan_pipeline(mist_space* S, int32_t hw, int32_t pp, mist_plan*
   if (hw < 0 || hw >= (int32_t)S->hw.size()) return fail(MIST_E_RANGE, "hardware sample out of range");
   if (pp < 0 || pp > MIST_MAX_STAGES) return fail(MIST_E_INVALID, "pp out of range");
   mist_status rc = have_results(S);
+  OnDevice on;
+  if (!rc) rc = begin_reads(S, S->stream, &on);
   if (rc) return rc;
   try {
     // The hardware sample's groups are consecutive; their points come back in one copy.
@@ -1388,12 +1426,12 @@ mist_status mist_plan_pipeline(mist_space* S, int32_t hw, int32_t pp, mist_plan*
     const size_t per = 1 + (size_t)S->A, n = (g1 - g0) * per;
     std::vector<PlanPoint> got(n);
     if (n) {
-      PlanPoint* w = (PlanPoint*)workspace(S, n * sizeof(PlanPoint), S->stream);
+      PlanPoint* w = (PlanPoint*)workspace(S, n * sizeof(PlanPoint));
       if (!w) return fail(MIST_E_NOMEM, "device allocation failed: frontier points");
       const int k = launch_points(eval_args(S), S->d_best_id, S->d_alpha_id, S->A, (int64_t)g0, (int64_t)(g1 - g0), w,
-                                  S->stream);
+                                  nullptr);
       if (k) return fail_hip((hipError_t)k, "frontier points launch");
-      rc = fetch(got.data(), w, n * sizeof(PlanPoint), S->stream, "frontier points");
+      rc = fetch(got.data(), w, n * sizeof(PlanPoint), "frontier points");
     } else {
       rc = wait_results(S);
     }
@@ -1428,25 +1466,27 @@ mist_status mist_get_buckets(mist_space* S, int64_t g0, int64_t n, uint64_t* ids
   if (g0 < 0 || n < 0 || g0 + n > (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group range");
   mist_status rc = n == 0 || (!ids && !objs && !masks) ? wait_results(S) : have_results(S);
   if (rc || n == 0) return rc;
+  OnDevice on;
+  rc = begin_reads(S, S->stream, &on);
+  if (rc) return rc;
   try {
     // The device tables hold 64 buckets per group: fewer are packed there first.
     const int NB = S->NB;
     const size_t words = (size_t)n * (size_t)NB;
-    hipStream_t st = S->stream;
     const uint64_t* src[2] = {S->d_bucket_id + g0 * 64, (const uint64_t*)S->d_bucket_obj + g0 * 64};
     void* dst[2] = {ids, objs};
     if (NB < 64 && (ids || objs)) {
-      uint64_t* w = (uint64_t*)workspace(S, 2 * words * sizeof(uint64_t), st);
+      uint64_t* w = (uint64_t*)workspace(S, 2 * words * sizeof(uint64_t));
       if (!w) return fail(MIST_E_NOMEM, "device allocation failed: buckets");
       for (int i = 0; i < 2; ++i) {
-        const int k = dst[i] ? launch_rows(src[i], NB, n, w + i * words, st) : 0;
+        const int k = dst[i] ? launch_rows(src[i], NB, n, w + i * words, nullptr) : 0;
         if (k) return fail_hip((hipError_t)k, "buckets launch");
         src[i] = w + i * words;
       }
     }
     for (int i = 0; i < 2 && !rc; ++i)
-      if (dst[i]) rc = fetch(dst[i], src[i], words * sizeof(uint64_t), st, "buckets");
-    if (!rc && masks) rc = fetch(masks, S->d_frontier + g0, (size_t)n * sizeof(uint64_t), st, "frontier masks");
+      if (dst[i]) rc = fetch(dst[i], src[i], words * sizeof(uint64_t), "buckets");
+    if (!rc && masks) rc = fetch(masks, S->d_frontier + g0, (size_t)n * sizeof(uint64_t), "frontier masks");
     return rc;
   } catch (const std::bad_alloc&) {
     return fail(MIST_E_NOMEM, "host allocation failed");
@@ -1457,16 +1497,18 @@ mist_status mist_get_pareto(mist_space* S, int64_t g, mist_result* out, int32_t 
   if (!S || !n_out) return fail(MIST_E_INVALID, "null argument");
   if (g < 0 || g >= (int64_t)S->groups.size()) return fail(MIST_E_RANGE, "group index");
   mist_status rc = have_results(S);
+  OnDevice on;
+  if (!rc) rc = begin_reads(S, S->stream, &on);
   if (rc) return rc;
   uint64_t mask = 0;
-  rc = fetch(&mask, S->d_frontier + g, sizeof(mask), S->stream, "frontier mask");
+  rc = fetch(&mask, S->d_frontier + g, sizeof(mask), "frontier mask");
   if (rc) return rc;
   *n_out = (int32_t)__builtin_popcountll(mask);
   if (*n_out > cap) return fail(MIST_E_RANGE, "output capacity too small");
   if (*n_out == 0) return MIST_OK;
   if (!out) return fail(MIST_E_INVALID, "out is null");
   mist_result row[MIST_MAX_BUCKETS];  // every bucket's winner, of which the staircase is kept
-  rc = fetch_results(S, S->d_bucket_id + g * 64, S->d_bucket_obj + g * 64, nullptr, 0, S->NB, row, S->stream);
+  rc = fetch_results(S, S->d_bucket_id + g * 64, S->d_bucket_obj + g * 64, nullptr, 0, S->NB, row);
   if (rc) return rc;
   int32_t w = 0;
   for (int j = 0; j < S->NB; ++j)

@@ -1,0 +1,281 @@
+// The library's host side on the CPU: mist_host.cpp itself, over a stand-in for the HIP runtime whose
+// device memory is host memory and whose kernels only record what they were given.  Each scenario
+// exercises what a healthy GPU run does not show (the order of reads, failing allocations and copies)
+// and exits with 0, or prints what differs.  Built and run by test_host_harness.py.
+
+#include "../paper_2503_19050_amd/csrc/mist_host.cpp"
+
+#include <cstdlib>
+#include <functional>
+
+namespace {
+
+struct Op {
+  char kind;        // 's' stream synchronized, 'c' copy, 'k' kernel
+  void* stream;
+  int device;
+};
+std::vector<Op> g_log;
+int g_device = 0;            // current device
+long g_copies_left = -1;     // copies that succeed before one fails (-1: all)
+long g_news_left = -1;       // allocations that succeed before one throws (-1: all)
+std::vector<DevTile> g_emit_tiles;  // what the last candidate pass was given
+uint64_t g_result_id = ~0ull;       // the id that the result kernels report
+
+void log(char kind, void* st) {
+  if (g_news_left < 0) g_log.push_back({kind, st, g_device});
+}
+
+hipError_t copy(void* dst, const void* src, size_t n, void* st) {
+  log('c', st);
+  if (g_copies_left == 0) return hipErrorUnknown;
+  if (g_copies_left > 0) --g_copies_left;
+  std::memcpy(dst, src, n);
+  return hipSuccess;
+}
+
+}  // namespace
+
+void* operator new(size_t n) {
+  if (g_news_left == 0) throw std::bad_alloc();
+  if (g_news_left > 0) --g_news_left;
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = std::malloc(n);
+  std::memset(*p, 0x7E, n);
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void* p) { return hipFree(p); }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { return copy(d, s, n, nullptr); }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) { return copy(d, s, n, st); }
+hipError_t hipStreamSynchronize(hipStream_t st) {
+  log('s', st);
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+  *d = g_device;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int d) {
+  g_device = d;
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
+  *v = 4;
+  return hipSuccess;
+}
+const char* hipGetErrorString(hipError_t) { return "stand-in error"; }
+hipError_t hipEventCreate(hipEvent_t*) { return hipErrorUnknown; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float*, hipEvent_t, hipEvent_t) { return hipErrorUnknown; }
+}
+
+namespace mist {
+
+int noalloc_scratch(void**) { return (int)hipErrorUnknown; }
+int launch_pairs(const EvalArgs& a, void* st) {
+  log('k', st);
+  if (a.pool_count) *a.pool_count = 0;
+  return 0;
+}
+int launch_eval(const EvalArgs&, int, int, void* st) { return log('k', st), 0; }
+int eval_blocks_per_cu(int, int) { return 4; }
+int search_blocks_per_cu(int, int) { return 4; }
+int launch_search(const EvalArgs& a, int, int mode, void* st) {
+  log('k', st);
+  if (mode == kModeEmit) {
+    g_emit_tiles.assign(a.tiles, a.tiles + a.n_tiles);
+    for (int32_t t = 0; t < a.n_tiles; ++t) {
+      a.cnt_tile[t] = 0;
+      a.tile_drop[t] = 0;
+      a.tile_live[t] = 0;
+    }
+  }
+  return 0;
+}
+int launch_reduce(const ReduceArgs& r, void* st) {  // every group: its best and all buckets are configuration 0
+  log('k', st);
+  for (int64_t g = 0; g < r.n_groups; ++g) {
+    r.best_id[g] = 0;
+    r.frontier[g] = 1;
+  }
+  return 0;
+}
+int launch_eval_ids(const EvalArgs&, const uint64_t*, int64_t, double*, void* st) { return log('k', st), 0; }
+int launch_filter(const EvalArgs&, const double*, const uint64_t*, FiltEntry*, void* st) { return log('k', st), 0; }
+int launch_results(const EvalArgs&, const uint64_t*, const double*, const uint64_t*, int32_t, int64_t n, mist_result* out, void* st) {
+  log('k', st);
+  for (int64_t i = 0; i < n; ++i) {
+    out[i] = mist_result{};
+    out[i].id = g_result_id;
+  }
+  return 0;
+}
+int launch_points(const EvalArgs&, const uint64_t*, const uint64_t*, int32_t n_alpha, int64_t, int64_t n, PlanPoint* out, void* st) {
+  log('k', st);
+  for (int64_t i = 0; i < n * (1 + n_alpha); ++i) out[i] = PlanPoint{g_result_id, 1.0, 0.0};
+  return 0;
+}
+int launch_rows(const uint64_t*, int32_t NB, int64_t n, uint64_t* out, void* st) {
+  log('k', st);
+  for (int64_t i = 0; i < n * NB; ++i) out[i] = 0;
+  return 0;
+}
+int launch_prefilter(uint64_t*, double*, uint64_t*, const int64_t*, int64_t, int64_t*, void* st) { return log('k', st), 0; }
+int exact_sort(const uint64_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*, int64_t, const int64_t*, const int64_t*, void* st) {
+  return log('k', st), 0;
+}
+int launch_compact(const uint64_t*, const double*, const uint64_t*, const int64_t*, const int32_t*, const uint8_t*,
+                   const int64_t*, int32_t, uint64_t*, double*, uint64_t*, void* st) {
+  return log('k', st), 0;
+}
+int launch_pool_place(const uint64_t*, const double*, const uint64_t*, const int32_t*, const int32_t*, int64_t,
+                      const uint8_t*, const int64_t*, uint64_t*, double*, uint64_t*, void* st) {
+  return log('k', st), 0;
+}
+int launch_front_scan(const uint32_t*, const uint64_t*, const double*, const uint64_t*, const int64_t*, const int64_t*,
+                      int64_t n_groups, uint64_t*, double*, uint64_t*, int64_t* cnt, void* st) {
+  log('k', st);
+  for (int64_t g = 0; g < n_groups; ++g) cnt[g] = 0;
+  return 0;
+}
+
+}  // namespace mist
+
+namespace {
+
+int g_bad = 0;
+void check(bool ok, const char* what) {
+  if (!ok) {
+    std::printf("differs: %s\n", what);
+    g_bad = 1;
+  }
+}
+
+mist_space* make_space(int64_t devices, int32_t n_buckets, int32_t n_alphas, int32_t n_ratios) {
+  mist_model_desc m{};
+  m.arch = MIST_ARCH_GPT;
+  m.n_layers = 6;
+  m.hidden = 512;
+  m.heads = m.kv_heads = 8;
+  m.ffn = 2048;
+  m.seq = 256;
+  m.vocab = 1000;
+  m.bytes_w = 2;
+  m.bytes_opt = 12;
+  m.flash = 1;
+  mist_hw_desc h{};
+  h.flops = 1e14;
+  h.mem_bytes = 1e10;
+  h.pcie_bw = 3e10;
+  h.link_bw = 1e11;
+  h.eta_max = 0.75;
+  h.n_half = 1024;
+  for (auto& row : h.phi)
+    for (double& v : row) v = 1.0;
+  const int32_t mb[] = {1, 2};
+  double r[MIST_MAX_RATIOS], al[] = {0.25, 0.75};
+  for (int32_t i = 0; i < n_ratios; ++i) r[i] = (double)i / n_ratios;
+  mist_space_desc s{};
+  s.n_devices = devices;
+  s.global_batch = 16 * devices;
+  s.mb = mb;
+  s.n_mb = 2;
+  s.ratios = r;
+  s.n_ratios = n_ratios;
+  s.n_buckets = n_buckets;
+  s.l_rule = MIST_L_FULL;
+  s.n_alphas = n_alphas;
+  s.alphas = al;
+  mist_space* S = nullptr;
+  const mist_status rc = mist_space_create(&m, &h, 1, &s, nullptr, &S);
+  if (rc) std::printf("create: %d %s\n", rc, mist_last_error());
+  return S;
+}
+
+struct Read {
+  const char* name;
+  std::function<mist_status(mist_space*)> call;
+};
+
+// Every call that reads results back.
+std::vector<Read> reads(std::vector<mist_result>& out, std::vector<uint64_t>& ids) {
+  out.resize(4096);
+  ids.resize(1 << 16);
+  return {
+      {"best", [&](mist_space* S) { return mist_get_best(S, 0, 1, out.data()); }},
+      {"alpha", [&](mist_space* S) { return mist_get_alpha(S, 0, 1, out.data()); }},
+      {"plan", [&](mist_space* S) { static mist_plan p; return mist_plan_pipeline(S, 0, 0, &p); }},
+      {"buckets", [&](mist_space* S) { return mist_get_buckets(S, 0, 1, ids.data(), nullptr, nullptr); }},
+      {"masks", [&](mist_space* S) { return mist_get_buckets(S, 0, 1, nullptr, nullptr, ids.data()); }},
+      {"pareto", [&](mist_space* S) { int32_t n = 0; return mist_get_pareto(S, 0, out.data(), 64, &n); }},
+  };
+}
+
+// Results are read on the null stream of the space's device, after the evaluation's stream was waited
+// for: whatever the caller queued on the null stream or a blocking stream since comes first.
+void order_of_reads() {
+  std::vector<mist_result> out;
+  std::vector<uint64_t> ids;
+  void* const side = (void*)0x1000;
+  void* const other = (void*)0x2000;
+  mist_space* S = make_space(2, 7, 2, 3);
+  check(mist_eval_space(S, side) == MIST_OK, "evaluation");
+  auto ordered = [&](const char* name, void* stream) {
+    size_t i = 0;
+    while (i < g_log.size() && !(g_log[i].kind == 's' && g_log[i].stream == stream)) check(g_log[i++].kind == 's', name);
+    check(i < g_log.size(), name);
+    bool any = false;
+    for (; i < g_log.size(); ++i) {
+      if (g_log[i].kind != 's') any = true;
+      check(g_log[i].kind == 's' || (g_log[i].stream == nullptr && g_log[i].device == 0), name);
+    }
+    check(any, name);
+    check(g_log.back().kind == 's' && g_log.back().stream == nullptr, name);
+  };
+  for (int device = 0; device < 2; ++device) {
+    for (const Read& r : reads(out, ids)) {
+      g_device = device;
+      g_log.clear();
+      check(r.call(S) == MIST_OK, r.name);
+      ordered(r.name, side);
+      check(g_device == device, r.name);
+    }
+    g_device = 0;
+  }
+  check(mist_eval_pareto_exact(S, other) == MIST_OK, "exact frontier");
+  int64_t n = 0;
+  g_log.clear();
+  check(mist_get_pareto_exact(S, 0, out.data(), 64, &n) == MIST_OK && n == 0, "exact staircase");
+  ordered("exact staircase", other);
+  mist_space_destroy(S);
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const struct {
+    const char* name;
+    void (*run)();
+  } all[] = {{"order_of_reads", order_of_reads}};
+  for (const auto& s : all)
+    if (argc == 2 && !std::strcmp(argv[1], s.name)) {
+      s.run();
+      return g_bad;
+    }
+  std::printf("no such scenario\n");
+  return 2;
+}

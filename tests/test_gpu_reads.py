@@ -1,0 +1,91 @@
+"""Reading results while the evaluation that forms them is a captured graph (GPU, through the C ABI)."""
+
+import numpy as np
+import pytest
+
+from paper_2503_19050_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "a GPU is required"
+    torch.cuda.init()
+    return torch
+
+
+class _Blocks:
+    """Device memory from torch tensors that the test can fill."""
+
+    def __init__(self, torch):
+        from paper_2503_19050_amd import mist
+        self.torch, self.held = torch, {}
+
+        def alloc(nbytes, stream, ctx):
+            t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
+            self.held[t.data_ptr()] = t
+            return t.data_ptr()
+
+        def free(ptr, ctx):
+            del self.held[ptr]
+
+        self.cb = (mist.ALLOC_FN(alloc), mist.FREE_FN(free))
+        self.struct = mist.Allocator(self.cb[0], self.cb[1], None)
+
+    def fill_results(self, S, value):
+        """Fills the space's per-group results and bucket tables, which every evaluation rewrites."""
+        n = S.n_groups
+        sizes = {8 * n, 8 * 64 * n, 8 * n * max(S.n_alphas, 1)}
+        hit = [t.fill_(value) for t in self.held.values() if t.numel() in sizes]
+        assert len(hit) >= 5
+        self.torch.cuda.synchronize()
+
+
+def _captured(torch, monkeypatch):
+    """(blocks, space, graph of its first evaluation, results of an eager evaluation)."""
+    from paper_2503_19050_amd import mist
+    wl = W.workload("tiny")
+    wl["space"]["alphas"] = [0.0, 0.3, 1.0]
+    with mist.from_workload(wl) as E:
+        E.eval()
+        want = _results(E)
+    blocks = _Blocks(torch)
+    monkeypatch.setattr(mist.Space, "_torch_allocator", lambda self: blocks.struct)
+    S = mist.from_workload(wl)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        S.eval()
+    return blocks, S, graph, want
+
+
+def _results(S):
+    best = S.best_array()
+    ids, objs, masks = S.buckets()
+    return {"best": best["id"].tolist(), "obj": best["obj"].tolist(), "ids": ids.tolist(), "objs": objs.tolist(),
+            "masks": masks.tolist(), "alpha": S.alpha(), "plan": S.plan(0),
+            "pareto": [S.pareto(g) for g in range(0, S.n_groups, 7)]}
+
+
+@pytest.mark.parametrize("first", ["best", "buckets", "alpha", "plan", "pareto"])
+def test_reads_follow_a_replay_on_the_default_stream(first, torch_cuda, monkeypatch):
+    """The graph is captured on one stream and replayed on the default one, behind other work: every
+    read sees the replay's results."""
+    torch = torch_cuda
+    blocks, S, graph, want = _captured(torch, monkeypatch)
+    x = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    read = {"best": lambda: S.best_array()["id"].tolist(), "buckets": lambda: S.buckets()[0].tolist(),
+            "alpha": S.alpha, "plan": lambda: S.plan(0), "pareto": lambda: S.pareto(0)}[first]
+    ref = {"best": want["best"], "buckets": want["ids"], "alpha": want["alpha"], "plan": want["plan"],
+           "pareto": want["pareto"][0]}[first]
+    for replay in range(3):
+        print("replay", replay, first, flush=True)
+        blocks.fill_results(S, 0xFF)  # every id MIST_NONE until the replay runs
+        for _ in range(20):
+            x @ x
+        graph.replay()
+        assert read() == ref
+        assert _results(S) == want
+    S.close()

@@ -1,0 +1,36 @@
+"""The library's host code over a stand-in for the HIP runtime (CPU): host_harness.cpp compiles
+mist_host.cpp against it and runs one scenario per test."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2503_19050_amd", "csrc")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include/hip"),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def harness(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("harness") / "host_harness")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__", "-w",
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", "/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "host_harness.cpp"), os.path.join(CSRC, "mist_plan.cpp"),
+                    "-o", exe], check=True)
+    return exe
+
+
+def run(harness, *args):
+    r = subprocess.run([harness, *args], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, (r.stdout + r.stderr)[-2000:])
+    return r.stdout
+
+
+def test_results_are_read_behind_the_null_stream(harness):
+    """Every read waits for the evaluation's stream, then runs on the null stream of the space's device
+    whichever device is current, and leaves that device current."""
+    run(harness, "order_of_reads")
