@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void k_results(EvalArgs a, const uint64_t* __r
   mist_result r = {};
   r.id = ids[i];
   r.obj = objs[i];
-  if (r.id == kNone) {
+  if (r.id >= a.n_configs) {  // kNone, or no configuration (results never written): the host refuses it
     r.t = r.d = r.mem = __builtin_huge_val();
     r.bucket = -1;
     r.cfg.hw = -1;
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_points(EvalArgs a, const uint64_t* __re
   const int64_t g = g0 + i / (1 + n_alpha);
   const int q = (int)(i % (1 + n_alpha));
   PlanPoint p{q == 0 ? best[g] : alpha[g * n_alpha + q - 1], 0.0, 0.0};
-  if (p.id != kNone) {
+  if (p.id < a.n_configs) {  // else kNone, or an id that the host refuses
     const OneVal v = eval_one(a, p.id);
     p.t = v.t;
     p.d = v.d;

@@ -672,6 +672,10 @@ mist_status fetch(void* dst, const void* src, size_t bytes, const char* what) {
   return e == hipSuccess ? MIST_OK : fail_hip(e, what);
 }
 
+// Whether a result's id is one that an evaluation writes.  Results that no evaluation has written yet (it is
+// captured in a graph that has not run) hold anything; the kernels below form nothing for such an id.
+bool is_result(const mist_space* S, uint64_t id) { return id == MIST_NONE || id < S->n_configs; }
+
 // Results of n configurations whose ids and objectives (with n_alpha > 0: weighted values) lie on the
 // device, formed there.
 mist_status fetch_results(mist_space* S, const uint64_t* ids, const double* objs, const uint64_t* key, int32_t n_alpha,
@@ -683,9 +687,12 @@ mist_status fetch_results(mist_space* S, const uint64_t* ids, const double* objs
   if (k) return fail_hip((hipError_t)k, "results launch");
   const mist_status rc = fetch(out, w, (size_t)n * sizeof(mist_result), "results");
   if (rc) return rc;
-  for (int64_t i = 0; i < n; ++i)
-    if (out[i].pad) return fail(MIST_E_DEVICE, "re-evaluated configuration differs");
-  return MIST_OK;
+  bool differs = false;
+  for (int64_t i = 0; i < n; ++i) {
+    if (!is_result(S, out[i].id)) return fail(MIST_E_RANGE, "id out of range");
+    differs |= out[i].pad != 0;
+  }
+  return differs ? fail(MIST_E_DEVICE, "re-evaluated configuration differs") : MIST_OK;
 }
 
 }  // namespace
@@ -1436,6 +1443,8 @@ mist_status mist_plan_pipeline(mist_space* S, int32_t hw, int32_t pp, mist_plan*
       rc = wait_results(S);
     }
     if (rc) return rc;
+    for (const PlanPoint& p : got)
+      if (!is_result(S, p.id)) return fail(MIST_E_RANGE, "id out of range");
     std::vector<mist_stage_point> pts;
     pts.reserve(n);
     for (size_t g = g0; g < g1; ++g) {

@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kReduceBlock) void k_filter(EvalArgs a, const doubl
   FiltEntry f;
   f.pm = below;
   f.bobj = obj;
-  f.bmem = id == kNone ? __builtin_huge_val() : eval_one(a, id).mem;
+  f.bmem = id < a.n_configs ? eval_one(a, id).mem : __builtin_huge_val();  // kNone, or a table never written
   filt[g * 64 + lane] = f;
 }
 

@@ -264,13 +264,32 @@ void order_of_reads() {
   mist_space_destroy(S);
 }
 
+// Ids that no evaluation wrote are refused.
+void ids_out_of_range() {
+  std::vector<mist_result> out;
+  std::vector<uint64_t> ids;
+  mist_space* S = make_space(2, 7, 2, 3);
+  check(mist_eval_space(S, nullptr) == MIST_OK, "evaluation");
+  for (uint64_t id : {S->n_configs, (uint64_t)0x7F7F7F7F7F7F7F7F, (uint64_t)-2}) {
+    g_result_id = id;
+    for (const Read& r : reads(out, ids))
+      if (std::strcmp(r.name, "buckets") && std::strcmp(r.name, "masks"))  // raw tables: copied as they are
+        check(r.call(S) == MIST_E_RANGE, r.name);
+  }
+  for (uint64_t id : {(uint64_t)0, S->n_configs - 1, (uint64_t)-1}) {
+    g_result_id = id;
+    for (const Read& r : reads(out, ids)) check(r.call(S) == MIST_OK, r.name);
+  }
+  mist_space_destroy(S);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } all[] = {{"order_of_reads", order_of_reads}};
+  } all[] = {{"order_of_reads", order_of_reads}, {"ids_out_of_range", ids_out_of_range}};
   for (const auto& s : all)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       s.run();

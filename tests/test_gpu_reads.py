@@ -44,7 +44,7 @@ class _Blocks:
 
 
 def _captured(torch, monkeypatch):
-    """(blocks, space, graph of its first evaluation, results of an eager evaluation)."""
+    """(blocks, space, graph of its first evaluation, results of an eager evaluation, workload)."""
     from paper_2503_19050_amd import mist
     wl = W.workload("tiny")
     wl["space"]["alphas"] = [0.0, 0.3, 1.0]
@@ -57,7 +57,7 @@ def _captured(torch, monkeypatch):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         S.eval()
-    return blocks, S, graph, want
+    return blocks, S, graph, want, wl
 
 
 def _results(S):
@@ -73,7 +73,7 @@ def test_reads_follow_a_replay_on_the_default_stream(first, torch_cuda, monkeypa
     """The graph is captured on one stream and replayed on the default one, behind other work: every
     read sees the replay's results."""
     torch = torch_cuda
-    blocks, S, graph, want = _captured(torch, monkeypatch)
+    blocks, S, graph, want, _ = _captured(torch, monkeypatch)
     x = torch.randn(4096, 4096, device="cuda")
     torch.cuda.synchronize()
     read = {"best": lambda: S.best_array()["id"].tolist(), "buckets": lambda: S.buckets()[0].tolist(),
@@ -89,3 +89,25 @@ def test_reads_follow_a_replay_on_the_default_stream(first, torch_cuda, monkeypa
         assert read() == ref
         assert _results(S) == want
     S.close()
+
+
+def test_results_that_were_never_written_are_refused(torch_cuda, monkeypatch):
+    """The captured evaluation has not run: its results hold ids past the space, which the kernels check
+    and the calls refuse; after a replay they are read."""
+    from paper_2503_19050_amd import mist
+    blocks, S, graph, want, wl = _captured(torch_cuda, monkeypatch)
+    blocks.fill_results(S, 0x7F)
+    for read in (S.best_array, S.alpha, lambda: S.plan(0), lambda: S.pareto(0)):
+        with pytest.raises(mist.MistError) as e:
+            read()
+        assert e.value.status == -5
+    S.eval_pareto_exact()  # its filter reads the same ids
+    graph.replay()
+    assert _results(S) == want
+    S.eval_pareto_exact()
+    got = [S.pareto_exact(g) for g in range(S.n_groups)]
+    S.close()
+    with mist.from_workload(wl) as E:
+        E.eval()
+        E.eval_pareto_exact()
+        assert got == [E.pareto_exact(g) for g in range(E.n_groups)]

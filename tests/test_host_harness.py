@@ -34,3 +34,8 @@ def test_results_are_read_behind_the_null_stream(harness):
     """Every read waits for the evaluation's stream, then runs on the null stream of the space's device
     whichever device is current, and leaves that device current."""
     run(harness, "order_of_reads")
+
+
+def test_ids_past_the_space_are_refused(harness):
+    """Results that no evaluation has written are reported as MIST_E_RANGE, not decoded."""
+    run(harness, "ids_out_of_range")
