@@ -795,21 +795,23 @@ void build_cand_tiles(mist_space* S, int64_t resident_waves) {
   for (const DevGroup& g : S->groups) total += (uint64_t)g.n_pairs * (uint64_t)(g.l + 1) * per_unit_strips;
   bool single = false;
   const int64_t spt = (int64_t)tile_strips(S, total, resident_waves, false, &single);
-  S->cand_tiles.clear();
-  S->cand_first.clear();
+  std::vector<DevTile> tiles;  // swapped in when complete: a failed allocation leaves none behind
+  std::vector<int32_t> first;
   for (size_t gi = 0; gi < S->groups.size(); ++gi) {
     const DevGroup& g = S->groups[gi];
     const int64_t strips = (int64_t)g.n_pairs * (g.l + 1) * (int64_t)per_unit_strips;
-    S->cand_first.push_back((int32_t)S->cand_tiles.size());
+    first.push_back((int32_t)tiles.size());
     for (int64_t u = 0; u < strips; u += spt) {
       DevTile t{};
       t.group = (int32_t)gi;
       t.strip_begin = (int32_t)u;
       t.strip_end = (int32_t)std::min<int64_t>(strips, u + spt);
-      S->cand_tiles.push_back(t);
+      tiles.push_back(t);
     }
   }
-  S->cand_first.push_back((int32_t)S->cand_tiles.size());
+  first.push_back((int32_t)tiles.size());
+  S->cand_tiles.swap(tiles);
+  S->cand_first.swap(first);
 }
 
 // Work items of the persistent evaluation grid in tile order per XCD.  Item i < n_waves is the

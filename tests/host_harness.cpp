@@ -283,13 +283,37 @@ void ids_out_of_range() {
   mist_space_destroy(S);
 }
 
+// The candidate tiles are whole or absent, whichever host allocation fails.
+void candidate_tiles() {
+  mist_space* S = make_space(4, 64, 0, 3);
+  for (long k = 0;; ++k) {
+    bool thrown = false;
+    g_news_left = k;
+    try {
+      build_cand_tiles(S, 16);
+    } catch (const std::bad_alloc&) {
+      thrown = true;
+    }
+    g_news_left = -1;
+    check(thrown ? S->cand_first.empty() && S->cand_tiles.empty()
+                 : S->cand_first.size() == S->groups.size() + 1 && (size_t)S->cand_first.back() == S->cand_tiles.size(),
+          "candidate tiles");
+    if (!thrown) {
+      check(k > 8, "allocations that can fail");
+      break;
+    }
+  }
+  mist_space_destroy(S);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } all[] = {{"order_of_reads", order_of_reads}, {"ids_out_of_range", ids_out_of_range}};
+  } all[] = {{"order_of_reads", order_of_reads}, {"ids_out_of_range", ids_out_of_range},
+             {"candidate_tiles", candidate_tiles}};
   for (const auto& s : all)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       s.run();

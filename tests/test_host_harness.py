@@ -39,3 +39,8 @@ def test_results_are_read_behind_the_null_stream(harness):
 def test_ids_past_the_space_are_refused(harness):
     """Results that no evaluation has written are reported as MIST_E_RANGE, not decoded."""
     run(harness, "ids_out_of_range")
+
+
+def test_candidate_tiles_are_whole_or_absent(harness):
+    """A host allocation that fails while the exact frontier's tiles are cut leaves no partial table."""
+    run(harness, "candidate_tiles")
