@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -147,6 +148,7 @@ struct mist_space {
   int32_t device = 0;  // the HIP device the space was created on
   // exact frontier (mist_eval_pareto_exact)
   bool exact_done = false;
+  bool exact_ready = false;     // its tables are allocated and uploaded
   bool exact_launched = false;  // some call enqueued uploads of the host offset tables
   hipStream_t exact_stream = nullptr;
   std::vector<DevTile> cand_tiles;  // tiles of the candidate pass (build_cand_tiles)
@@ -206,6 +208,8 @@ namespace {
 // A device buffer owned by the space; `st` is the stream of its first use (see mist_allocator).
 void* dev_alloc(mist_space* S, size_t bytes, hipStream_t st) {
   if (bytes == 0) bytes = 256;
+  // Room for the entry first: a failed host allocation throws before there is a block to lose.
+  if (S->dev_buffers.size() == S->dev_buffers.capacity()) S->dev_buffers.reserve(2 * S->dev_buffers.size() + 16);
   void* p = nullptr;
   if (S->custom_alloc) {
     p = S->alloc.alloc(bytes, (void*)st, S->alloc.ctx);
@@ -1089,6 +1093,25 @@ static int32_t mode_grid(const mist_space* S, int mode, size_t n) {
   return (int32_t)std::max<int64_t>(1, std::min<int64_t>(resident_blocks(S, mode), (int64_t)(n + kWaves - 1) / kWaves));
 }
 
+// The exact frontier's tables, allocated by its first call and kept.
+static std::array<void**, 21> exact_buffers(mist_space* S) {
+  return {(void**)&S->d_filt,      (void**)&S->d_cand_tiles, (void**)&S->d_cnt_tile,   (void**)&S->d_tile_off,
+          (void**)&S->d_tile_end,  (void**)&S->d_list,       (void**)&S->d_seg,        (void**)&S->d_seg_end,
+          (void**)&S->d_live,      (void**)&S->d_front_cnt,  (void**)&S->d_slab_begin, (void**)&S->d_slab_key,
+          (void**)&S->d_slab_obj,  (void**)&S->d_slab_id,    (void**)&S->d_pool_count, (void**)&S->d_pool_key,
+          (void**)&S->d_pool_obj,  (void**)&S->d_pool_id,    (void**)&S->d_pool_tile,  (void**)&S->d_pool_rank,
+          (void**)&S->d_tile_drop};
+}
+
+static void release_exact(mist_space* S) {
+  for (void** b : exact_buffers(S)) {
+    dev_free_one(S, *b);
+    *b = nullptr;
+  }
+  if (S->h_pinned) (void)hipHostFree(S->h_pinned);
+  S->h_pinned = nullptr;
+}
+
 mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
   if (!S) return fail(MIST_E_INVALID, "space is null");
   mist_status rc = wait_results(S);
@@ -1105,7 +1128,8 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
     }
     S->exact_done = false;
     S->front_cnt.clear();
-    if (!S->d_filt) {
+    if (!S->exact_ready) {
+      release_exact(S);  // what a call that failed midway left
       // Windows: ceil(configurations / div) slots per tile.
       const int64_t R2 = (int64_t)S->R * S->R;
       auto slots = [&](int64_t div) {
@@ -1163,28 +1187,21 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
           S->h_drop = (uint8_t*)(S->h_pool_count + 1);
         }
       }
-      void** bufs[] = {(void**)&S->d_filt,      (void**)&S->d_cand_tiles, (void**)&S->d_cnt_tile,   (void**)&S->d_tile_off,
-                       (void**)&S->d_tile_end,  (void**)&S->d_list,       (void**)&S->d_seg, (void**)&S->d_seg_end, (void**)&S->d_live,
-                       (void**)&S->d_front_cnt, (void**)&S->d_slab_begin, (void**)&S->d_slab_key,
-                       (void**)&S->d_slab_obj,  (void**)&S->d_slab_id,    (void**)&S->d_pool_count,
-                       (void**)&S->d_pool_key,  (void**)&S->d_pool_obj,   (void**)&S->d_pool_id,
-                       (void**)&S->d_pool_tile, (void**)&S->d_pool_rank,  (void**)&S->d_tile_drop};
       bool ok = S->h_pinned != nullptr;
-      for (void** b : bufs) ok = ok && *b;
+      for (void** b : exact_buffers(S)) ok = ok && *b;
       if (!ok) {  // free what was allocated: the next call starts over
-        for (void** b : bufs) {
-          dev_free_one(S, *b);
-          *b = nullptr;
-        }
-        if (S->h_pinned) (void)hipHostFree(S->h_pinned);
-        S->h_pinned = nullptr;
+        release_exact(S);
         return fail(MIST_E_NOMEM, "device allocation failed: exact frontier");
       }
       hipError_t e = copy_sync(S->d_slab_begin, S->h_slab_begin.data(), (nt + 1) * sizeof(int64_t),
                                hipMemcpyHostToDevice);
       if (e == hipSuccess)
         e = copy_sync(S->d_cand_tiles, S->cand_tiles.data(), nt * sizeof(DevTile), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return fail_hip(e, "exact frontier: windows");
+      if (e != hipSuccess) {
+        release_exact(S);
+        return fail_hip(e, "exact frontier: windows");
+      }
+      S->exact_ready = true;
     }
     // Pass 1: every tile writes its candidates to its window and counts them.
     EvalArgs ea = eval_args(S);
@@ -1241,9 +1258,14 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
     S->h_seg[ng] = off;
     if (off >= ((int64_t)1 << 32)) return fail(MIST_E_RANGE, "exact frontier: more than 2^32 candidates");
     if (off > S->cand_cap) {
-      void* old[] = {S->d_cand_key, S->d_cand_id, S->d_key_sorted, S->d_cand_obj, S->d_idx_in, S->d_idx_out,
-                     S->d_front_key, S->d_front_id, S->d_front_obj};
-      for (void* p : old) dev_free_one(S, p);
+      void** old[] = {(void**)&S->d_cand_key, (void**)&S->d_cand_id,  (void**)&S->d_key_sorted,
+                      (void**)&S->d_cand_obj, (void**)&S->d_idx_in,   (void**)&S->d_idx_out,
+                      (void**)&S->d_front_key, (void**)&S->d_front_id, (void**)&S->d_front_obj};
+      S->cand_cap = 0;
+      for (void** p : old) {
+        dev_free_one(S, *p);
+        *p = nullptr;
+      }
       const size_t n = (size_t)off;
       S->d_cand_key = (uint64_t*)dev_alloc(S, n * 8, st);
       S->d_cand_id = (uint64_t*)dev_alloc(S, n * 8, st);
@@ -1254,12 +1276,9 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream) {
       S->d_front_key = (uint64_t*)dev_alloc(S, n * 8, st);
       S->d_front_id = (uint64_t*)dev_alloc(S, n * 8, st);
       S->d_front_obj = (double*)dev_alloc(S, n * 8, st);
+      for (void** p : old)
+        if (!*p) return fail(MIST_E_NOMEM, "device allocation failed: exact frontier candidates");
       S->cand_cap = off;
-      if (!S->d_cand_key || !S->d_cand_id || !S->d_key_sorted || !S->d_cand_obj || !S->d_idx_in ||
-          !S->d_idx_out || !S->d_front_key || !S->d_front_id || !S->d_front_obj) {
-        S->cand_cap = 0;
-        return fail(MIST_E_NOMEM, "device allocation failed: exact frontier candidates");
-      }
     }
     const int32_t n_list = S->n_list;
     S->exact_launched = true;

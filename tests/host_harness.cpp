@@ -17,8 +17,10 @@ struct Op {
 };
 std::vector<Op> g_log;
 int g_device = 0;            // current device
-long g_copies_left = -1;     // copies that succeed before one fails (-1: all)
-long g_news_left = -1;       // allocations that succeed before one throws (-1: all)
+long g_copies_left = -1;     // copies that succeed before one fails (-1: none does)
+long g_mallocs_left = -1;    // device allocations that succeed before one fails (-1: none does)
+int g_emit_count = 0;        // candidates that the candidate pass reports per tile
+long g_news_left = -1;       // allocations that succeed before one throws (-1: none does)
 std::vector<DevTile> g_emit_tiles;  // what the last candidate pass was given
 uint64_t g_result_id = ~0ull;       // the id that the result kernels report
 
@@ -28,8 +30,7 @@ void log(char kind, void* st) {
 
 hipError_t copy(void* dst, const void* src, size_t n, void* st) {
   log('c', st);
-  if (g_copies_left == 0) return hipErrorUnknown;
-  if (g_copies_left > 0) --g_copies_left;
+  if (g_copies_left >= 0 && g_copies_left-- == 0) return hipErrorUnknown;
   std::memcpy(dst, src, n);
   return hipSuccess;
 }
@@ -37,16 +38,18 @@ hipError_t copy(void* dst, const void* src, size_t n, void* st) {
 }  // namespace
 
 void* operator new(size_t n) {
-  if (g_news_left == 0) throw std::bad_alloc();
-  if (g_news_left > 0) --g_news_left;
+  if (g_news_left >= 0 && g_news_left-- == 0) throw std::bad_alloc();
   if (void* p = std::malloc(n ? n : 1)) return p;
   throw std::bad_alloc();
 }
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return std::malloc(n ? n : 1); }
+void operator delete(void* p, const std::nothrow_t&) noexcept { std::free(p); }
 void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+  if (g_mallocs_left >= 0 && g_mallocs_left-- == 0) return hipErrorOutOfMemory;
   *p = std::malloc(n);
   std::memset(*p, 0x7E, n);
   return hipSuccess;
@@ -99,7 +102,7 @@ int launch_search(const EvalArgs& a, int, int mode, void* st) {
   if (mode == kModeEmit) {
     g_emit_tiles.assign(a.tiles, a.tiles + a.n_tiles);
     for (int32_t t = 0; t < a.n_tiles; ++t) {
-      a.cnt_tile[t] = 0;
+      a.cnt_tile[t] = g_emit_count;
       a.tile_drop[t] = 0;
       a.tile_live[t] = 0;
     }
@@ -306,6 +309,44 @@ void candidate_tiles() {
   mist_space_destroy(S);
 }
 
+// Whichever copy, device allocation or host allocation of the first exact frontier fails, the call reports
+// it and the next one starts over with whole tables.
+void exact_tables() {
+  mist_space* R = make_space(4, 64, 0, 3);
+  build_cand_tiles(R, resident_blocks(R, kModeEmit) * kWaves);
+  long* const failing[] = {&g_copies_left, &g_mallocs_left, &g_news_left};
+  const mist_status codes[] = {MIST_E_DEVICE, MIST_E_NOMEM, MIST_E_NOMEM};
+  g_emit_count = 1;
+  for (int f = 0; f < 3; ++f) {
+    for (long k = 0;; ++k) {
+      mist_space* S = make_space(4, 64, 0, 3);
+      check(mist_eval_space(S, nullptr) == MIST_OK, "evaluation");
+      *failing[f] = k;
+      const mist_status rc = mist_eval_pareto_exact(S, nullptr);
+      *failing[f] = -1;
+      if (rc) {
+        check(rc == codes[f], "status");
+        int64_t n = 0;
+        check(mist_get_pareto_exact(S, 0, nullptr, 0, &n) == MIST_E_STATE, "no frontier after a failed call");
+      }
+      for (int again = 0; again < 2; ++again) {
+        g_emit_tiles.clear();
+        check(mist_eval_pareto_exact(S, nullptr) == MIST_OK, "the next call");
+        check(g_emit_tiles.size() == R->cand_tiles.size() &&
+                  !std::memcmp(g_emit_tiles.data(), R->cand_tiles.data(), R->cand_tiles.size() * sizeof(DevTile)),
+              "the tiles of the next call");
+        check(S->cand_cap == (int64_t)R->cand_tiles.size() && S->d_front_obj, "the candidates of the next call");
+      }
+      mist_space_destroy(S);
+      if (!rc) {
+        check(k > (f == 1 ? 28 : 4), "calls that can fail");
+        break;
+      }
+    }
+  }
+  mist_space_destroy(R);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -313,7 +354,7 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } all[] = {{"order_of_reads", order_of_reads}, {"ids_out_of_range", ids_out_of_range},
-             {"candidate_tiles", candidate_tiles}};
+             {"candidate_tiles", candidate_tiles}, {"exact_tables", exact_tables}};
   for (const auto& s : all)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       s.run();

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir
 @pytest.fixture(scope="module")
 def harness(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("harness") / "host_harness")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__", "-w",
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address", "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__", "-w",
                     "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", "/opt/rocm/include",
                     os.path.join(ROOT, "tests", "host_harness.cpp"), os.path.join(CSRC, "mist_plan.cpp"),
                     "-o", exe], check=True)
@@ -25,7 +25,8 @@ def harness(tmp_path_factory):
 
 
 def run(harness, *args):
-    r = subprocess.run([harness, *args], capture_output=True, text=True, timeout=300)
+    r = subprocess.run([harness, *args], capture_output=True, text=True, timeout=300,
+                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
     assert r.returncode == 0, (r.returncode, (r.stdout + r.stderr)[-2000:])
     return r.stdout
 
@@ -44,3 +45,9 @@ def test_ids_past_the_space_are_refused(harness):
 def test_candidate_tiles_are_whole_or_absent(harness):
     """A host allocation that fails while the exact frontier's tiles are cut leaves no partial table."""
     run(harness, "candidate_tiles")
+
+
+def test_exact_frontier_starts_over_after_a_failure(harness):
+    """Every copy, device allocation and host allocation of the first exact frontier fails in turn; the
+    next call has whole tables."""
+    run(harness, "exact_tables")
