@@ -19,7 +19,8 @@ SOURCES = [os.path.join(CSRC, "mist_host.cpp"), os.path.join(CSRC, "mist_plan.cp
            os.path.join(CSRC, "mist_exact.hip"), os.path.join(CSRC, "mist_corun.hip"),
            os.path.join(CSRC, "mist_probe.hip"), os.path.join(CSRC, "mist_noalloc.hip")]
 LIBS = ["-lrocblas"]  # the calibration's GEMMs
-HEADERS = [os.path.join(CSRC, "mist_internal.h"), os.path.join(CSRC, "mist_device.h"), os.path.join(INCLUDE, "mist.h")]
+HEADERS = [os.path.join(CSRC, "mist_internal.h"), os.path.join(CSRC, "mist_device.h"),
+           os.path.join(CSRC, "mist_bounds.h"), os.path.join(INCLUDE, "mist.h")]
 
 ARCH = "gfx950"
 FLAGS = [

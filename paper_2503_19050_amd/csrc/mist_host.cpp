@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "mist.h"
+#include "mist_bounds.h"
 #include "mist_internal.h"
 
 using namespace mist;
@@ -57,31 +58,6 @@ constexpr int64_t kWindowSlots = (int64_t)1 << 27;  // and all windows together,
 constexpr int64_t kPoolSlots = (int64_t)1 << 27;    // overflow pool of the candidate pass, at most
 constexpr int64_t kTailPercent = 10;          // share of each group's strips in small tiles
 constexpr int64_t kStripAlign = kWaveTile;    // strips per tile: a multiple of the wave
-
-// Least directional derivative of Algorithm 1's time along (0, 0, 1, 1), both host streams growing
-// alike.  For a given order in which the streams finish, the time is linear in the stream times:
-// each phase lasts the scaled time of the stream that finishes, and every other member's standalone
-// time falls by that length over its factor.  The time is continuous where orders change (a phase of
-// length 0), so along a segment it never grows by less than the least slope over the orders it meets:
-// all (first = 0), those that start with GPU-GPU (1), or with GPU-GPU and then compute (2).
-double host_slope(const double phi[16][4], int first) {
-  int ord[4] = {0, 1, 2, 3};
-  double least = std::numeric_limits<double>::infinity();
-  do {
-    if ((first >= 1 && ord[0] != 1) || (first >= 2 && ord[1] != 0)) continue;
-    double x[4] = {0.0, 0.0, 1.0, 1.0}, T = 0.0;
-    int mask = 15;
-    for (int i = 0; i < 3; ++i) {
-      const double ov = x[ord[i]] * phi[mask][ord[i]];
-      T += ov;
-      for (int j = 0; j < 4; ++j)
-        if (mask >> j & 1) x[j] -= ov / phi[mask][j];
-      mask &= ~(1 << ord[i]);
-    }
-    least = std::min(least, T + x[ord[3]]);
-  } while (std::next_permutation(ord, ord + 4));
-  return least - 1e-9 * (1.0 + std::fabs(least));
-}
 
 int popcount4(int v) { return (v & 1) + ((v >> 1) & 1) + ((v >> 2) & 1) + ((v >> 3) & 1); }
 
@@ -489,7 +465,7 @@ std::string enumerate(mist_space* S, mist_status* code) {
     for (int mask = 0; mask < 16; ++mask)
       for (int j = 0; j < 4; ++j)
         if (popcount4(mask) >= 2 && (mask >> j & 1) && h.phi[mask][j] > 0x1p16) d.lbs = 0.0;
-    for (int f = 0; f < 3; ++f) d.slope[f] = host_slope(h.phi, f);
+    host_slopes(h.phi, d.slope);
     for (int j = 0; j < MIST_MAX_MB; ++j) d.ieta[j] = 0.0;
     for (size_t j = 0; j < S->mb.size(); ++j) {
       if (h.eta_max == 0.0) {  // measured efficiency of this microbatch size

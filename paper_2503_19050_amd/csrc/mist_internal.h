@@ -56,7 +56,7 @@ struct DevHw {
                              // with slowdown factors above 2^16
   double slope[3];           // least growth of Algorithm 1's time when both host streams grow by one:
                              // over all orders in which the streams finish, those in which GPU-GPU
-                             // is first, and those in which compute follows it
+                             // is first, and those in which compute follows it; -inf: no bound
   double ieta[MIST_MAX_MB];  // 1 / eta(b) per microbatch index
   double edge[MIST_MAX_BUCKETS];     // E_j; +inf past NB
   // Row per co-running pattern (bit j = stream j runs): phi[4] then psi[4].  Patterns of

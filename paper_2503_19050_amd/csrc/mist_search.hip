@@ -1,5 +1,6 @@
 // The bounded search over large spaces, and the exact frontier's candidate pass (gfx950).
 
+#include "mist_bounds.h"
 #include "mist_device.h"
 
 namespace mist {
@@ -292,8 +293,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
     // slope sl by which it grows at least.  Another optimizer ratio's is that time with both host
     // streams longer by the same (r - r0) So / PCIe, and Algorithm 1's time is continuous and
     // piecewise linear in that length, with no slope below slope0 (slope1 when GPU-GPU finishes first at
-    // the smallest ratio, slope2 when compute follows: as the host streams grow, it stays so).  With a
-    // negative slope the bound falls until it meets the host streams, which grow with slope 1.
+    // the smallest ratio, slope2 when compute follows: as the host streams grow, it stays so).
     [[maybe_unused]] auto first_times = [&](const KnownRow& fr, double C, double gf, int ia, double h0, double d0, bool free,
                                             double& T10, double& sl) {
       int f0 = kFormGeneral;
@@ -732,8 +732,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
             double T10, sl;
             const double h0 = hs + Hx0, d0 = ds + Dx0;
             first_times(fr, C, gf, ia, h0, d0, !(col | acol), T10, sl);
-            const double neg = __builtin_fmin(sl, 0.0);
-            const double T1m = __builtin_fmax(T1l, T10 + neg * (1.0 / (1.0 - neg)) * (T10 - __builtin_fmax(h0, d0)));
+            const double T1m = __builtin_fmax(T1l, any_length(T10, sl, __builtin_fmax(h0, d0)));
             col = col & alive(Blo + SO, __builtin_fma(Gm1, tv, T1m), th);
             acol = acol & (__builtin_fma(T1m, lbs, -tv) <= dls);
             if (!__builtin_amdgcn_ballot_w64(col | acol)) continue;
