@@ -337,6 +337,10 @@ mist_status mist_eval_ids_noalloc(mist_space* S, const uint64_t* ids, int64_t n,
 mist_status mist_set_timing(mist_space* S, int32_t on);
 mist_status mist_read_timing(mist_space* S, double* eval_ms, double* reduce_ms, int64_t* n_evals);
 
+/* Whether mist_eval_space searches the space with bounds (*bounded = 1) or evaluates every
+ * configuration (0); the results are the same.  Chosen by the sizes of the space when it is created. */
+mist_status mist_search_info(const mist_space* S, int32_t* bounded);
+
 /* Tile t of the evaluation kernel: its group, the global id of its first configuration and its
  * configuration count (a tile covers consecutive ids of one group).  Errors: MIST_E_RANGE. */
 mist_status mist_tile_info(const mist_space* S, int32_t t, int64_t* group, uint64_t* first_id, int64_t* n_configs);

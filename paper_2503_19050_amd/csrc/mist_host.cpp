@@ -1624,6 +1624,12 @@ mist_status mist_read_timing(mist_space* S, double* eval_ms, double* reduce_ms, 
   return MIST_OK;
 }
 
+mist_status mist_search_info(const mist_space* S, int32_t* bounded) {
+  if (!S || !bounded) return fail(MIST_E_INVALID, "null argument");
+  *bounded = S->bounded ? 1 : 0;
+  return MIST_OK;
+}
+
 mist_status mist_tile_info(const mist_space* S, int32_t t, int64_t* group, uint64_t* first_id, int64_t* n_configs) {
   if (!S) return fail(MIST_E_INVALID, "space is null");
   if (t < 0 || (size_t)t >= S->tiles.size()) return fail(MIST_E_RANGE, "tile out of range");

@@ -28,7 +28,7 @@ EXPORTS = [
     "mist_plan_points", "mist_plan_pipeline", "mist_eval_pareto_exact", "mist_get_pareto_exact", "mist_exact_info",
     "mist_corun_create", "mist_corun_run", "mist_corun_reduce", "mist_corun_measure", "mist_corun_destroy",
     "mist_fit_phi", "mist_interference", "mist_measure_eta", "mist_probe_fp64",
-    "mist_tile_info", "mist_debug_eval_tiles", "mist_eval_ids_noalloc", "mist_exact_group_sizes",
+    "mist_search_info", "mist_tile_info", "mist_debug_eval_tiles", "mist_eval_ids_noalloc", "mist_exact_group_sizes",
 ]
 
 PROBE_KINDS = {"add": 0, "mul": 1, "fma": 2, "min": 3, "max": 4, "cmp": 5}
@@ -176,6 +176,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         L.mist_interference.argtypes = [dp, dp, dp]
         L.mist_measure_eta.argtypes = [P(ModelDesc), ip, ctypes.c_int32, ctypes.c_int32, ctypes.c_double,
                                        ctypes.c_int32, dp, dp]
+        L.mist_search_info.argtypes = [vp, ip]
         L.mist_tile_info.argtypes = [vp, ctypes.c_int32, P(ctypes.c_int64), P(ctypes.c_uint64), P(ctypes.c_int64)]
         L.mist_debug_eval_tiles.argtypes = [vp, P(ctypes.c_int32), ctypes.c_int32, P(ctypes.c_double),
                                             ctypes.c_int64, vp]
@@ -415,6 +416,12 @@ class Space:
                                                     len(ids), out.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
                                                     ctypes.c_void_p(_stream_handle(stream))))
         return out
+
+    def searched(self) -> bool:
+        """Whether the evaluation searches the space with bounds (else it evaluates every configuration)."""
+        b = ctypes.c_int32()
+        _check(self.L, self.L.mist_search_info(self.h, ctypes.byref(b)))
+        return b.value != 0
 
     def tile_info(self, t: int) -> dict:
         g = ctypes.c_int64()

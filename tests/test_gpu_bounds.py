@@ -3,8 +3,10 @@
 Large spaces are evaluated by a search that decides units, strips, columns and configurations by
 bounds; smaller ones evaluate every configuration, which the oracle checks elsewhere.  Here a random
 space is given enough hardware samples that it takes the search, and each sample's groups are
-compared bit for bit (bucket tables, best, staircases, weight samples) with the same samples in
-spaces small enough to be evaluated in full, whose groups and ids are the same up to their base.
+compared bit for bit (bucket tables, best, weight samples) with the same samples in spaces small
+enough to be evaluated in full, whose groups and ids are the same up to their base.  Which way each
+space went is asserted.  The exact staircases, whose candidate pass is the search's in either, are
+compared with the oracle's.
 """
 
 import copy
@@ -26,14 +28,15 @@ def torch_cuda():
     return torch
 
 
-BOUNDED, BOUNDED_ALPHA = 1.3e8, 2.6e8   # configurations from which the search runs, and some more
+BOUNDED, BOUNDED_ALPHA = 1.3e8, 6.3e8   # configurations from which the search runs, and some more
+ORACLE = 3_000_000                      # configurations of a group whose staircase the oracle forms
 FULL = 1.0e8                            # and below which every configuration is evaluated
 
 
 def _space(seed, R, n_alpha, factors):
     """A random model and space with R ratios and groups large enough for the search, and enough
-    hardware samples: budgets from far too small to roomy, factors seeded, all 1, up to 50 or one
-    of 2^17 (where bounds on the objective are off)."""
+    hardware samples: budgets from far too small to roomy, factors seeded, all 1, up to 50, up to 2^12
+    (where the slope bound is off) or one of 2^17 (where bounds on the objective are off)."""
     rng = np.random.default_rng(seed)
     wl = W.random_space(seed)
     grid = [0.0] if rng.random() < 0.7 else [0.04]
@@ -61,35 +64,52 @@ def _space(seed, R, n_alpha, factors):
             hw["phi"] = [[1.0] * 4 for _ in range(16)]
         elif factors == "large":
             hw["phi"] = [[1.0 + 49.0 * rng.random() for _ in range(4)] for _ in range(16)]
+        elif factors == "wide":
+            hw["phi"] = [[2.0 ** (12.0 * rng.random()) for _ in range(4)] for _ in range(16)]
         elif factors == "huge":
             hw["phi"][int(rng.choice([13, 15, 5, 12]))][int(rng.choice([0, 2, 3]))] = 2.0 ** 17
         wl["hws"].append(hw)
     return wl, o.n_configs, o.n_groups
 
 
-def _results(S, n_alpha, stairs):
+def _results(S, n_alpha):
     S.eval()
     ids, objs, masks = S.buckets()
     best = S.best_array()
     out = {"ids": ids, "objs": objs, "masks": masks, "best": best["id"].copy(), "bobj": best["obj"].copy()}
     if n_alpha:
-        al = S.alpha()
-        out["aid"] = np.array([[r["id"] for r in row] for row in al], dtype=np.uint64)
-        out["aobj"] = np.array([[r["obj"] for r in row] for row in al])
-    if stairs:
-        S.eval_pareto_exact()
-        out["exact"] = [[(r["id"], r["obj"], r["mem"]) for r in S.pareto_exact(g)] for g in stairs]
+        from paper_2503_19050_amd import mist
+        raw = (mist.Result * (S.n_groups * n_alpha))()
+        assert S.L.mist_get_alpha(S.h, 0, S.n_groups, raw) == 0
+        al = np.ctypeslib.as_array(raw)
+        out["aid"], out["aobj"] = al["id"].copy(), al["obj"].copy()
     return out
+
+
+def _check_stairs(S, wl, n1, g1):
+    """The exact staircases of a few groups, of different machines, against the oracle's."""
+    S.eval_pareto_exact()
+    n = 0
+    for g in range(S.n_groups // 26, S.n_groups, max(1, S.n_groups // 13)):
+        if S.group_key(g)["size"] > ORACLE:
+            continue
+        h = g // g1
+        want = O.Oracle(dict(wl, hws=[wl["hws"][h]])).pareto_exact(g - h * g1)
+        got = S.pareto_exact(g)
+        assert [r["id"] for r in got] == [int(i) + h * n1 for i in want["id"]], g
+        assert [r["obj"] for r in got] == want["obj"].tolist() and [r["mem"] for r in got] == want["mem"].tolist(), g
+        n += 1
+    return n
 
 
 @pytest.mark.parametrize("R, n_alpha, factors", [
     (2, 0, "seeded"), (3, 0, "large"), (4, 0, "unit"), (5, 0, "huge"), (5, 0, "seeded"), (6, 0, "large"),
     (7, 0, "seeded"), (9, 0, "unit"), (11, 0, "seeded"), (16, 0, "large"),
-    (4, 1, "seeded"), (5, 3, "large"), (6, 16, "seeded"), (9, 8, "huge"), (11, 2, "unit"),
+    (4, 1, "seeded"), (5, 3, "large"), (6, 16, "seeded"), (7, 4, "wide"), (9, 8, "huge"), (11, 2, "unit"),
 ])
 def test_search_equals_full_evaluation(R, n_alpha, factors, torch_cuda):
     from paper_2503_19050_amd import mist
-    found = 0
+    found = stairs = 0
     for seed in range(7000 + 100 * R, 7100 + 100 * R):
         made = _space(seed, R, n_alpha, factors)
         if made is None:
@@ -97,8 +117,9 @@ def test_search_equals_full_evaluation(R, n_alpha, factors, torch_cuda):
         wl, n1, g1 = made
         print("bounds: R", R, "seed", seed, "hw", len(wl["hws"]), "configurations per hw", n1, flush=True)
         S = mist.from_workload(wl)
-        stairs = list(range(0, S.n_groups, max(1, S.n_groups // 12)))
-        got = _results(S, n_alpha, stairs)
+        assert S.searched()
+        got = _results(S, n_alpha)
+        stairs += _check_stairs(S, wl, n1, g1)
         S.close()
         part = max(1, int(FULL // n1) if n1 < FULL else 1)
         none = np.uint64(mist.MIST_NONE)
@@ -106,8 +127,8 @@ def test_search_equals_full_evaluation(R, n_alpha, factors, torch_cuda):
             sub = dict(wl, hws=wl["hws"][h:h + part])
             g0, base = h * g1, np.uint64(h * n1)
             F = mist.from_workload(sub)
-            sel = [g for g in stairs if g0 <= g < g0 + F.n_groups]
-            want = _results(F, n_alpha, [g - g0 for g in sel])
+            assert not F.searched()
+            want = _results(F, n_alpha)
             n = F.n_groups
             F.close()
             shift = lambda x: np.where(x == none, none, x + base)  # noqa: E731
@@ -117,11 +138,10 @@ def test_search_equals_full_evaluation(R, n_alpha, factors, torch_cuda):
             assert np.array_equal(got["best"][g0:g0 + n], shift(want["best"]))
             assert np.array_equal(got["bobj"][g0:g0 + n], want["bobj"])
             if n_alpha:
-                assert np.array_equal(got["aobj"][g0:g0 + n], want["aobj"])
-                assert np.array_equal(got["aid"][g0:g0 + n], shift(want["aid"]))
-            for g, w in zip(sel, want["exact"]):
-                assert got["exact"][stairs.index(g)] == [(i + int(base), o, m) for i, o, m in w], g
+                at = slice(g0 * n_alpha, (g0 + n) * n_alpha)
+                assert np.array_equal(got["aobj"][at], want["aobj"])
+                assert np.array_equal(got["aid"][at], shift(want["aid"]))
         found += 1
         if found == 2:
             break
-    assert found == 2
+    assert found == 2 and stairs > 0
