@@ -51,6 +51,8 @@ constexpr int64_t kTilesPerWave = 12;         // full-size tiles per resident wa
 // they cost, and large enough groups (use_bounds).
 constexpr uint64_t kBoundedConfigs = 120000000, kBoundedPerGroup = 8000;
 constexpr uint64_t kBoundedAlphaConfigs = 450000000, kBoundedAlphaPerGroup = 30000;
+constexpr uint64_t kBoundedAlphaFew = 600000000;  // with samples, on at most kFewDevices devices
+constexpr int64_t kFewDevices = 4;
 constexpr int64_t kMaxTiles = 131072;         // and tiles per space, at most
 constexpr int64_t kWindowDiv = 8;             // exact frontier: candidate window of a tile,
                                               // 1/kWindowDiv of its configurations
@@ -680,15 +682,24 @@ mist_status fetch_results(mist_space* S, const uint64_t* ids, const double* objs
 namespace {
 
 // Whether the bounded search evaluates the space, or every configuration is evaluated.  Measured over
-// spaces of 1e6 to 3e9 configurations (evaluation kernel, every configuration / bounded search): with
-// buckets alone 0.5-1.1x below 1e8, 1.2-1.9x from 1.2e8 to 3e8, 2-12x above 6e8; below about 8,000
-// configurations per group the tables and the seeds of a group cost more than its bounds save
-// (0.55x at 1,500, 0.97x at 8,400).  With weight samples, whose smallest delta is hard to bound, 0.65-1.1x
-// from 2.5e8 to 4.5e8 (mean 0.85x), 1.1-2.6x above (mean 1.4x; 0.92x and 0.97x in two of 35 spaces, of 2 and
-// 4 devices), and 0.85-0.93x in groups of fewer than about 30,000.
+// spaces of 1e6 to 4e9 configurations: time of evaluating every configuration / of the bounded search,
+// geometric mean (least to most; spaces slower than 0.98 of all).  With buckets alone 0.5-1.1x below 1e8, and
+//   configurations  1.2-2e8                2-3e8                 3-6e8                 6-9e8                 above
+//   D >= 6          1.6 (0.75-3.7; 4/39)   2.0 (1.2-5.0; 0/32)   2.6 (1.2-5.0; 0/68)   3.0 (1.7-6.4; 0/29)   3.7 (1.2-10; 0/32)
+//   D <= 4          1.4 (0.58-5.2; 19/102) 1.8 (0.77-5.9; 8/60)  2.2 (0.81-9.2; 3/120) 2.3 (0.92-7.0; 3/36)  3.5 (1.2-9.6; 0/32)
+// The slower ones are mostly small models on few devices, whose configurations all fit the budget and hide
+// their transfers behind compute: the bounds tell little apart there, and no size tells these spaces from
+// those that gain most.  Below about 8,000 configurations per group the tables and the seeds of a group
+// cost more than its bounds save (0.55x at 1,500, 0.97x at 8,400).  With weight samples, whose smallest delta is
+// hard to bound, 0.65-1.1x from 2.5e8 to 4.5e8 (mean 0.85), 0.85-0.93x in groups of fewer than about 30,000, and
+//   configurations  4.5-6e8                6-9e8                 above
+//   D >= 6          1.3 (0.88-1.9; 4/23)   1.5 (1.06-2.2; 0/19)  2.0 (1.02-3.9; 0/78)
+//   D <= 4          1.1 (0.67-3.5; 15/32)  1.2 (0.69-4.3; 8/29)  1.6 (0.68-7.8; 7/89)
+// where half of the spaces of the last row's first entry lose: every configuration is evaluated there.
 bool use_bounds(const mist_space* S) {
   const uint64_t n = S->n_configs, g = (uint64_t)S->groups.size();
-  if (S->A > 0) return g > 0 && n >= kBoundedAlphaConfigs && n / g >= kBoundedAlphaPerGroup;
+  if (S->A > 0)
+    return g > 0 && n >= (S->D <= kFewDevices ? kBoundedAlphaFew : kBoundedAlphaConfigs) && n / g >= kBoundedAlphaPerGroup;
   return g > 0 && n >= kBoundedConfigs && n / g >= kBoundedPerGroup;
 }
 

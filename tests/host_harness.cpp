@@ -347,6 +347,29 @@ void exact_tables() {
   mist_space_destroy(R);
 }
 
+// Which spaces are searched with bounds: the lines of use_bounds, from both sides.
+void search_rule() {
+  const struct {
+    int64_t D;
+    int32_t A;
+    uint64_t n, groups;
+    bool want;
+  } rows[] = {
+      {16, 0, 120000000, 1000, true},  {16, 0, 119999999, 1000, false}, {2, 0, 120000000, 1000, true},
+      {16, 0, 120000000, 15000, true}, {16, 0, 120000000, 15001, false}, {16, 0, 0, 0, false},
+      {8, 4, 450000000, 1000, true},   {8, 4, 449999999, 1000, false},  {5, 4, 450000000, 1000, true},
+      {4, 4, 599999999, 1000, false},  {4, 4, 600000000, 1000, true},   {2, 1, 500000000, 100, false},
+      {8, 4, 450000000, 15000, true},  {8, 4, 450000000, 15001, false}, {4, 4, 600000000, 20001, false}};
+  for (const auto& r : rows) {
+    mist_space S;
+    S.D = r.D;
+    S.A = r.A;
+    S.n_configs = r.n;
+    S.groups.resize(r.groups);
+    check(use_bounds(&S) == r.want, "which spaces are searched");
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -354,7 +377,7 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } all[] = {{"order_of_reads", order_of_reads}, {"ids_out_of_range", ids_out_of_range},
-             {"candidate_tiles", candidate_tiles}, {"exact_tables", exact_tables}};
+             {"candidate_tiles", candidate_tiles}, {"exact_tables", exact_tables}, {"search_rule", search_rule}};
   for (const auto& s : all)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       s.run();

@@ -51,3 +51,8 @@ def test_exact_frontier_starts_over_after_a_failure(harness):
     """Every copy, device allocation and host allocation of the first exact frontier fails in turn; the
     next call has whole tables."""
     run(harness, "exact_tables")
+
+
+def test_which_spaces_are_searched(harness):
+    """The sizes from which a space is searched with bounds, by device count and weight samples."""
+    run(harness, "search_rule")
