@@ -623,6 +623,7 @@ int eval_blocks_per_cu(int R, int mode) {
 }
 
 int launch_eval(const EvalArgs& a, int blocks, int mode, void* stream) {
+  if (mode != kModeBuckets && mode != kModeAlpha && mode != kModeDump) return (int)hipErrorInvalidValue;
   if (a.n_tiles <= 0) return 0;
   hipStream_t st = (hipStream_t)stream;
   switch (a.R) {

@@ -871,6 +871,7 @@ int search_blocks_per_cu(int R, int mode) {
 }
 
 int launch_search(const EvalArgs& a, int blocks, int mode, void* stream) {
+  if (mode < kModeBuckets || mode > kModeSeedAlpha) return (int)hipErrorInvalidValue;
   if (a.n_tiles <= 0) return 0;
   hipStream_t st = (hipStream_t)stream;
   switch (a.R) {

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from paper_2503_19050_amd import mist
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2503_19050_amd", "csrc")
 
@@ -56,3 +58,26 @@ def test_exact_frontier_starts_over_after_a_failure(harness):
 def test_which_spaces_are_searched(harness):
     """The sizes from which a space is searched with bounds, by device count and weight samples."""
     run(harness, "search_rule")
+
+
+LAUNCHES = r"""
+#include <cstdio>
+#include "mist_internal.h"
+int main() {
+  mist::EvalArgs a{};  // no tile: nothing is launched
+  a.R = 5;
+  for (int mode = -1; mode < 8; ++mode) std::printf("%d %d\n", mist::launch_eval(a, 1, mode, nullptr), mist::launch_search(a, 1, mode, nullptr));
+}
+"""
+
+
+def test_launches_refuse_variants_they_do_not_have(tmp_path):
+    """The evaluation kernel has the bucket, weight-sample and dump variants; the search has all six."""
+    (tmp_path / "l.cpp").write_text(LAUNCHES)
+    exe = str(tmp_path / "l")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, str(tmp_path / "l.cpp"),
+                    mist.LIB_PATH, "-Wl,-rpath," + mist.PKG, "-Wl,--allow-shlib-undefined", "-o", exe], check=True)
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="")
+    out = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=120, check=True).stdout.split()
+    ok = [(int(e) == 0, int(s) == 0) for e, s in zip(out[::2], out[1::2])]
+    assert ok == [(m in (0, 1, 3), 0 <= m <= 5) for m in range(-1, 8)]
