@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
   constexpr bool SD = MODE == kModeSeed || MODE == kModeSeedAlpha;
   constexpr bool AL = MODE == kModeAlpha || MODE == kModeSeedAlpha;
   constexpr bool BK = MODE == kModeBuckets || SD || AL;
-  constexpr bool QU = !SD && !DM;  // columns go through the queue
+  constexpr bool QU = !SD;  // columns go through the queue
   constexpr int R2 = R * R;
   constexpr int kUnits = unit_slots<MODE>();
   __shared__ double s_tab[kWaves][16 * kLdsRow + 2 * kTab2];
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
       const double ra = s_ratio[ia], qa = s_ratio[R + ia];
       const double hs = __builtin_fma(ra, T.A, T.HW) * iP, ds = __builtin_fma(ra, T.A, T.I.DG) * iP;
       configs(T, on & ((it >> 17 & 1u) != 0u), on & ((it >> 18 & 1u) != 0u), ia, hs, ds,
-              __builtin_fma(ra, T.A2, qa * T.KA), tv, 0);
+              __builtin_fma(ra, T.A2, qa * T.KA), tv, DM ? (int)(it >> 19 & 7u) : 0);
       qn -= n;
       if (BK && changed) refresh();
     };
@@ -744,7 +744,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_search(EvalArgs a, const double* 
             if (col | acol) {
               const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
               s_qt[wave][pos] = tv;
-              s_qi[wave][pos] = (uint32_t)slot | (uint32_t)rem2 << 5 | (uint32_t)ia << 13 | (col ? 1u << 17 : 0u) | (acol ? 1u << 18 : 0u);
+              s_qi[wave][pos] = (uint32_t)slot | (uint32_t)rem2 << 5 | (uint32_t)ia << 13 | (col ? 1u << 17 : 0u) | (acol ? 1u << 18 : 0u) |
+                                 (DM ? (uint32_t)fst << 19 : 0u);
             }
             qn += __builtin_popcountll(m);
           } else {
