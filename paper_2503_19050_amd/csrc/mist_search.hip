@@ -11,13 +11,9 @@ namespace {
 // them.
 constexpr int kPoolChunk = 256;
 
+// Every lane of the wave calls this.
 __device__ __forceinline__ void pool_holes(const EvalArgs& a, unsigned long long base, int used, int lane) {
-  // The active lanes share the work (lanes past a ragged tile's last strip are inactive).
-  const unsigned long long ex = __builtin_amdgcn_read_exec();
-  const int n_act = __builtin_popcountll(ex);
-  const int r = (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(ex >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)ex, 0u));
-  (void)lane;
-  for (int i = used + r; i < kPoolChunk; i += n_act) {
+  for (int i = used + lane; i < kPoolChunk; i += 64) {
     const unsigned long long pos = base + (unsigned long long)i;
     if (pos < (unsigned long long)a.pool_cap) a.pool_tile[pos] = -1;
   }
