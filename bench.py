@@ -31,19 +31,27 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6   # 256 CUs x 128 FP64 FLOP/clk (64 FMA lanes) x 
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 FLOPS_FILE = os.path.join(ROOT, "tests", "golden", "flops_per_config.json")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
-# Counter records of the bounded search, which evaluates the workloads listed there.
+# Counter records of the bounded search, of workloads that it evaluates.
 SEARCH_FILE = os.path.join(ROOT, "profiles", "search.json")
-SEARCH_SRC = [os.path.join(ROOT, "paper_2503_19050_amd", "csrc", f) for f in ("mist_search.hip", "mist_device.h")]
-KERNEL_SRC = os.path.join(ROOT, "paper_2503_19050_amd", "csrc", "mist_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2503_19050_amd", "csrc")
+KERNEL_SRC = [os.path.join(CSRC, f) for f in ("mist_kernels.hip", "mist_device.h")]
+SEARCH_SRC = [os.path.join(CSRC, f) for f in ("mist_search.hip", "mist_device.h", "mist_bounds.h")]
 
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+def source_hash(paths) -> str:
+    h = hashlib.sha256()
+    for p in paths:
+        with open(p, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
+
+
 def kernel_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    return source_hash(KERNEL_SRC)
 
 
 def flops_per_config(name: str):
@@ -87,19 +95,15 @@ def traffic_record(name: str, n_launch_configs: int):
 
 
 def search_record(name: str):
-    """(whether the bounded search evaluates the workload, its committed counter record if taken on
-    the current source): HBM bytes per launch, and per configuration of the space the FP64
-    operations and VALU instructions it executes."""
+    """The committed counter record of the bounded search on a workload, if it was taken on the current
+    source: HBM bytes per launch, and per configuration of the space the FP64 operations and VALU
+    instructions it executes."""
     try:
         with open(SEARCH_FILE) as f:
             rec = json.load(f)[name]
     except (OSError, KeyError, ValueError):
-        return False, None
-    h = hashlib.sha256()
-    for p in SEARCH_SRC:
-        with open(p, "rb") as f:
-            h.update(f.read())
-    return True, rec if rec.get("kernel_sha") == h.hexdigest()[:16] else None
+        return None
+    return rec if rec.get("kernel_sha") == source_hash(SEARCH_SRC) else None
 
 
 def _oracle_for(wl: dict, seconds: float, shard: int, n_shards: int):
@@ -262,7 +266,8 @@ def main() -> int:
     k2_avg = k2_ms / n
     fpc, fscratch = flops_per_config(wl["name"])
     roofline = None
-    searched, srec = search_record(wl["name"])
+    searched = S.searched()
+    srec = search_record(wl["name"]) if searched else None
     if searched:
         # The bounded search decides most configurations without forming their times, so no rate is
         # formed from the operations of the full definition: the roofline is that of the FP64
@@ -319,15 +324,15 @@ def main() -> int:
             runs.append((time.perf_counter() - t0) * 1e3)
         runs.sort()
         ms = runs[len(runs) // 2]
-        # The row's rate: configurations of the space per second of the whole pass.  Tiles that
-        # cannot hold a candidate are skipped, so it is not an evaluation rate and no FP64 peak
-        # fraction is derived from it.
+        # The row's rate: configurations of the space per second of the whole pass.  What cannot hold a
+        # candidate is skipped by bounds, so it is not an evaluation rate and no FP64 peak fraction is
+        # derived from it.
         exact = {"ms_per_run": ms, "runs": len(runs), "value": S.n_configs / (ms / 1e3), "unit": "configs/s",
                  **S.exact_info(),
                  "what": "exact time-vs-memory frontier of every group after the evaluation: candidate filter, "
-                         "live tiles, one candidate pass of the evaluation kernel over them (candidates past a tile's window go to an "
-                         "overflow pool; a tile with a candidate that finds no place in either is evaluated again), exact "
-                         "pre-filter, segmented sort by memory, scan; host "
+                         "one candidate pass of the bounded search over all tiles (tiles_live: those of which some unit may hold "
+                         "a candidate; candidates past a tile's window go to an overflow pool; a tile with a candidate that "
+                         "finds no place in either is evaluated again), exact pre-filter, segmented sort by memory, scan; host "
                          "wall time including its one synchronisation"}
 
     alpha = None
@@ -348,11 +353,12 @@ def main() -> int:
         a_total = start.elapsed_time(end)
         a_k1, a_k2, a_n = SA.read_timing()
         SA.set_timing(False)
-        a_fpc = None if fpc is None or searched else fpc + 3.0 * A   # + per sample: (1-alpha)*d and one fma (shared levels)
+        # + per sample: (1-alpha)*d and one fma (shared levels); no unit where most are excluded by bounds
+        a_fpc = None if fpc is None or SA.searched() else fpc + 3.0 * A
         a_k1_avg = a_k1 / a_n
         alpha = {"n_alphas": A, "value": S.n_configs / (a_total / args.steps / 1e3), "unit": "configs/s",
                  "ms_per_step": a_total / args.steps, "eval_kernel_ms": a_k1_avg, "reduce_kernel_ms": a_k2 / a_n,
-                 "flops_per_config": a_fpc,
+                 "searched": SA.searched(), "flops_per_config": a_fpc,
                  "frac": None if a_fpc is None else a_fpc * S.n_configs / (a_k1_avg / 1e3) / 1e12 / FP64_VECTOR_PEAK_TFLOPS}
         SA.close()
 

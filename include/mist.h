@@ -116,7 +116,8 @@ typedef struct mist_space_desc {
                             full-size tile of the evaluation kernel, at least (0: chosen
                             by the size of the space) */
   int32_t max_blocks;    /* cap on the evaluation kernel's grid (0: every block that fits on the
-                            device at once) */
+                            device at once); a searched space's first launch, which samples each
+                            group for its first bounds, has a wave per group in any case */
   int32_t cand_window;   /* exact frontier, results do not depend on it: each tile first writes
                             its candidates to a window of ceil(configurations / cand_window)
                             slots (0: 8, raised as needed to keep all windows within 2^27 slots),
@@ -279,10 +280,10 @@ mist_status mist_eval_pareto_exact(mist_space* S, void* hip_stream);
 mist_status mist_get_pareto_exact(mist_space* S, int64_t g, mist_result* out, int64_t cap, int64_t* n_out);
 
 /* Sizes of the last exact frontier, for diagnostics and measurement: the candidates of the
- * candidate pass (all groups), those the pre-filter kept, the tiles the candidate pass
- * evaluated (those that may hold a candidate) and the tiles evaluated a second time because
- * a candidate found no place in its window or the overflow pool.  Waits for mist_eval_pareto_exact; any pointer may
- * be NULL.  Errors: MIST_E_INVALID, MIST_E_STATE, MIST_E_DEVICE, MIST_E_NOMEM. */
+ * candidate pass (all groups), those the pre-filter kept, the tiles of the candidate pass (its own,
+ * not those of mist_tile_info) of which some (pair, recomputed layers, ZeRO level) may hold a
+ * candidate by its bounds, and the tiles evaluated a second time because a candidate found no
+ * place in its window or the overflow pool.  Waits for mist_eval_pareto_exact; any pointer may be NULL.  Errors: MIST_E_INVALID, MIST_E_STATE, MIST_E_DEVICE, MIST_E_NOMEM. */
 mist_status mist_exact_info(mist_space* S, int64_t* n_candidates, int64_t* n_kept, int32_t* n_tiles_live,
                             int32_t* n_tiles_again);
 

@@ -363,8 +363,8 @@ class Space:
         return c[:n], k[:n]
 
     def exact_info(self) -> dict:
-        """Sizes of the last exact frontier: candidates, those the pre-filter kept, tiles the
-        candidate pass evaluated, and tiles evaluated a second time."""
+        """Sizes of the last exact frontier: candidates, those the pre-filter kept, tiles of the
+        candidate pass that may hold one, and tiles evaluated a second time."""
         c, k, v, t = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int32(), ctypes.c_int32()
         _check(self.L, self.L.mist_exact_info(self.h, ctypes.byref(c), ctypes.byref(k), ctypes.byref(v),
                                               ctypes.byref(t)))

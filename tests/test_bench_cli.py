@@ -82,3 +82,25 @@ def test_committed_counter_records_match_the_kernel_source():
     flops, _ = bench.flops_per_config("llama42b-d128-hw64")
     assert 30.0 < rec["executed_fp64_per_config"] < flops
     assert rec["executed_fp64_per_config"] < rec["valu_per_config"] < 200.0
+
+
+def test_committed_search_records_match_the_source():
+    """profiles/search.json holds records of the bounded search, taken on the committed sources."""
+    with open(bench.SEARCH_FILE) as f:
+        recs = json.load(f)
+    assert "llama42b-d128-hw64" in recs
+    for name, rec in recs.items():
+        assert rec["kernel_sha"] == bench.source_hash(bench.SEARCH_SRC), name
+        assert bench.search_record(name) == rec
+        assert rec["seed_bytes"] + rec["search_bytes"] == rec["bytes_per_launch"]
+    assert bench.search_record("no such workload") is None
+
+
+def test_records_depend_on_every_source_of_their_kernel(monkeypatch, tmp_path):
+    """Changing any source of a kernel, the shared device header included, drops its records."""
+    for paths in (bench.KERNEL_SRC, bench.SEARCH_SRC):
+        assert any(p.endswith("mist_device.h") for p in paths)
+        for p in paths:
+            other = tmp_path / os.path.basename(p)
+            other.write_bytes(open(p, "rb").read() + b"// changed\n")
+            assert bench.source_hash([str(other) if q == p else q for q in paths]) != bench.source_hash(paths)
