@@ -332,8 +332,8 @@ mist_status mist_eval_ids_noalloc(mist_space* S, const uint64_t* ids, int64_t n,
 /* Kernel timing.  mist_set_timing(S, 1) waits for pending work and starts recording HIP
  * events around the two kernels of every later mist_eval_space, on the evaluation stream;
  * mist_read_timing waits for the recorded evaluations and returns the summed durations (ms)
- * of the evaluation kernel and of the group-reduction kernel and their count, then starts a
- * new record.  mist_set_timing(S, 0) stops recording.  Errors: MIST_E_STATE (timing off),
+ * of the evaluation kernel (of a searched space: with the launch that samples its groups) and of the
+ * group-reduction kernel and their count, then starts a new record.  mist_set_timing(S, 0) stops recording.  Errors: MIST_E_STATE (timing off),
  * MIST_E_DEVICE. */
 mist_status mist_set_timing(mist_space* S, int32_t on);
 mist_status mist_read_timing(mist_space* S, double* eval_ms, double* reduce_ms, int64_t* n_evals);
