@@ -23,13 +23,26 @@ namespace {
 
 thread_local std::string g_error;
 
-mist_status fail(mist_status code, const std::string& msg) {
-  g_error = msg;
+// Reporting an error never throws, so that running out of memory is reported too: the text is left out
+// when there is no room for it.
+mist_status fail(mist_status code, const char* msg) noexcept {
+  try {
+    g_error = msg;
+  } catch (...) {
+    g_error.clear();
+  }
   return code;
 }
 
-mist_status fail_hip(hipError_t e, const char* what) {
-  return fail(MIST_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
+mist_status fail(mist_status code, const std::string& msg) noexcept { return fail(code, msg.c_str()); }
+
+mist_status fail_hip(hipError_t e, const char* what) noexcept {
+  try {
+    g_error = std::string(what) + ": " + hipGetErrorString(e);
+  } catch (...) {
+    g_error.clear();
+  }
+  return MIST_E_DEVICE;
 }
 
 // Copies that accept an empty range (a space may have no group; a caller may ask for none).
@@ -1732,4 +1745,5 @@ const char* mist_last_error(void) { return g_error.c_str(); }
 
 namespace mist {
 __attribute__((visibility("hidden"))) mist_status lib_fail(mist_status code, const std::string& msg) { return fail(code, msg); }
+__attribute__((visibility("hidden"))) mist_status lib_fail(mist_status code, const char* msg) noexcept { return fail(code, msg); }
 }  // namespace mist

@@ -43,7 +43,7 @@
 #include "mist.h"
 
 namespace mist {
-__attribute__((visibility("hidden"))) mist_status lib_fail(mist_status code, const std::string& msg);  // sets the thread's error
+__attribute__((visibility("hidden"))) mist_status lib_fail(mist_status code, const char* msg) noexcept;  // sets the thread's error
 }
 
 namespace {

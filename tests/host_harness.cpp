@@ -21,6 +21,7 @@ long g_copies_left = -1;     // copies that succeed before one fails (-1: none d
 long g_mallocs_left = -1;    // device allocations that succeed before one fails (-1: none does)
 int g_emit_count = 0;        // candidates that the candidate pass reports per tile
 long g_news_left = -1;       // allocations that succeed before one throws (-1: none does)
+bool g_news_stay = false;    // and whether every later one throws as well
 std::vector<DevTile> g_emit_tiles;  // what the last candidate pass was given
 uint64_t g_result_id = ~0ull;       // the id that the result kernels report
 
@@ -38,7 +39,10 @@ hipError_t copy(void* dst, const void* src, size_t n, void* st) {
 }  // namespace
 
 void* operator new(size_t n) {
-  if (g_news_left >= 0 && g_news_left-- == 0) throw std::bad_alloc();
+  if (g_news_left >= 0 && g_news_left-- == 0) {
+    if (g_news_stay) g_news_left = 0;
+    throw std::bad_alloc();
+  }
   if (void* p = std::malloc(n ? n : 1)) return p;
   throw std::bad_alloc();
 }
@@ -347,6 +351,32 @@ void exact_tables() {
   mist_space_destroy(R);
 }
 
+// A call that runs out of host memory and finds none for its message either returns MIST_E_NOMEM.
+void out_of_memory() {
+  std::vector<mist_result> out;
+  std::vector<uint64_t> ids;
+  const auto calls = reads(out, ids);
+  std::vector<mist_stage_point> pts;
+  for (int32_t l = 1; l <= 6; ++l) pts.push_back({2, 1, 1, l, (uint64_t)l, 1.0 + l, 0.5});
+  mist_plan plan;
+  mist_space* S = make_space(4, 7, 2, 3);
+  check(mist_eval_space(S, nullptr) == MIST_OK, "evaluation");
+  const std::function<mist_status()> run[] = {[&] { return mist_eval_pareto_exact(S, nullptr); },
+                                              [&] { return mist_plan_points(pts.data(), (int64_t)pts.size(), 6, 0, &plan); },
+                                              [&] { return mist_plan_pipeline(S, 0, 0, &plan); },
+                                              [&] { return mist_get_best(S, 0, 1, out.data()); }};
+  for (const auto& f : run)
+    for (long k = 0;; ++k) {
+      g_news_stay = true;
+      g_news_left = k;
+      const mist_status rc = f();
+      g_news_left = -1;
+      check(rc == MIST_OK || rc == MIST_E_NOMEM, "status without memory");
+      if (rc == MIST_OK) break;
+    }
+  mist_space_destroy(S);
+}
+
 // Which spaces are searched with bounds: the lines of use_bounds, from both sides.
 void search_rule() {
   const struct {
@@ -377,7 +407,7 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } all[] = {{"order_of_reads", order_of_reads}, {"ids_out_of_range", ids_out_of_range},
-             {"candidate_tiles", candidate_tiles}, {"exact_tables", exact_tables}, {"search_rule", search_rule}};
+             {"candidate_tiles", candidate_tiles}, {"exact_tables", exact_tables}, {"search_rule", search_rule}, {"out_of_memory", out_of_memory}};
   for (const auto& s : all)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       s.run();
